@@ -190,147 +190,118 @@ __device__ __forceinline__ float corner_weight(const Cell &c, int dx, int dy, in
 // for its outstanding global stores and atomics, which stay in flight.
 __device__ __forceinline__ void lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup", "local"); }
 
-// Adjoint of trilinear interpolation for the 64 points held by the lanes of a wave, with
-// the contributions that land on the same vertex summed inside the wave before the atomic.
+// Adjoint of trilinear interpolation along a run of consecutive samples: the slot walk.
 //
-// Points come from consecutive samples along rays, so the lanes that touch one vertex form
-// runs of neighbouring lanes.  A (lane, corner) pair is the head of its run when the lane
-// before does not touch that vertex; the head walks forward over the following lanes while
-// they still touch the vertex, adds their weighted values (each lane's corner for that
-// vertex follows from its own cell), and alone issues the atomics.  Every contribution is
-// counted once: a non-head belongs to exactly one run, whose head reaches it.  All lanes
-// must call this (it shuffles); lanes with valid == false contribute nothing.
-// Whole-wave DPP shifts by one lane with zero fill (vector-ALU moves, no LDS round trip):
-// from_next: lane l takes lane l + 1's value (lane 63 takes 0); from_prev: lane l takes lane
-// l - 1's (lane 0 takes 0).  The empty asm keeps each shift a move of its own: the compiler
-// would otherwise fold it into the instruction that uses it.
-__device__ __forceinline__ int from_next(int x) {
-    int y = __builtin_amdgcn_update_dpp(0, x, 0x130, 0xF, 0xF, true);
-    asm volatile("" : "+v"(y));
-    return y;
+// Consecutive samples lie along a ray, so they share vertices with their neighbours.  A cell has
+// exactly one vertex of each parity class (x mod 2, y mod 2, z mod 2), and a vertex keeps its class
+// for as long as the walk stays in its cells: eight accumulators, one per class, hold the vertices of
+// the current cell, and one leaves (a single global atomic) only when the walk moves to a cell that
+// has another vertex of its class.  A group of GL = (8 / SL) NC adjacent lanes walks one run of samples,
+// lane = (classes, channel) with SL of the eight classes in registers; the lanes of one class hold
+// consecutive channels and those of the two z parities follow each other, so vertices of one column
+// that leave together leave as one contiguous span.  64 / GL groups per wave walk side by side.
+//
+// The samples' cells are staged in LDS first, one lane per sample (stage_cell): the float index of
+// the cell's low corner and the three fractions, each with the parity of its cell index in the
+// (otherwise clear) sign bit.
+__device__ __forceinline__ float4 stage_cell(const DevGrid &g, const Cell &c) {
+    const auto tag = [](float f, int i) {
+        return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, f) & 0x7fffffffu) | ((unsigned)i << 31));
+    };
+    return make_float4(__builtin_bit_cast(float, c.ix * g.sx + c.iy * g.sy + c.iz * g.cs), tag(c.fx, c.ix),
+                       tag(c.fy, c.iy), tag(c.fz, c.iz));
 }
-__device__ __forceinline__ int from_prev(int x) {
-    int y = __builtin_amdgcn_update_dpp(0, x, 0x138, 0xF, 0xF, true);
-    asm volatile("" : "+v"(y));
-    return y;
-}
-__device__ __forceinline__ float from_next(float x) { return __builtin_bit_cast(float, from_next(__builtin_bit_cast(int, x))); }
 
-template <int NC>
-__device__ __forceinline__ void scatter_wave(const DevGrid &g, bool valid, const Cell &cl, const float (&v)[NC],
-                                             int nch = NC) {
-    const int ln = lane();
-    const int px = from_prev(cl.ix), py = from_prev(cl.iy), pz = from_prev(cl.iz);
-    const bool pvalid = from_prev(valid ? 1 : 0) != 0;  // lane 0 has no predecessor
-    const int base = cl.ix * g.sx + cl.iy * g.sy + cl.iz * g.cs;
-    // The corners go in groups: with many channels four at a time, since their accumulators are the
-    // largest register set of the scatter and halving them lets more waves share a SIMD (the walk
-    // then runs once per group).
-    constexpr int CG = NC > 4 ? 4 : 8;
+template <int NC, int SL>
+struct SlotWalk {
+    static constexpr int GL = (8 / SL) * NC;  // lanes of a group
+    static constexpr int NG = 64 / GL;        // groups of a wave
+    static_assert(GL <= 64 && (SL == 1 || SL == 2 || SL == 4), "a group fits a wave");
+    int cur[SL];    // float offset (without the channel) of the vertex each slot holds
+    float acc[SL];  // its sum so far; 0 when nothing is held
+    int group, ch, hi;
+
+    __device__ __forceinline__ SlotWalk() {
+        group = lane() / GL;
+        const int r = lane() - group * GL;
+        hi = r / NC;
+        ch = r - hi * NC;
 #pragma unroll
-    for (int c0 = 0; c0 < 8; c0 += CG) {
-        float acc[CG][NC];
-        unsigned head = 0;  // bit cc: corner c0 + cc heads its run
-#pragma unroll
-        for (int cc = 0; cc < CG; ++cc) {
-            const int c = c0 + cc;
-            const int dx = (c >> 2) & 1, dy = (c >> 1) & 1, dz = c & 1;
-            const int ax = cl.ix + dx - px, ay = cl.iy + dy - py, az = cl.iz + dz - pz;
-            const bool prev_touches = pvalid && (unsigned)ax <= 1u && (unsigned)ay <= 1u && (unsigned)az <= 1u;
-            if (valid && !prev_touches) head |= 1u << cc;
-            const float w = corner_weight(cl, dx, dy, dz);
-#pragma unroll
-            for (int ch = 0; ch < NC; ++ch) acc[cc][ch] = w * v[ch];
-        }
-        unsigned active = head;
-        // the values of lane ln + k, moved one lane further each step (zeros past lane 63, so the
-        // validity flag of a lane beyond the wave reads as false)
-        int nx = cl.ix, ny = cl.iy, nz = cl.iz, nval = valid ? 1 : 0;
-        Cell nc = cl;
-        float nv[NC];
-#pragma unroll
-        for (int ch = 0; ch < NC; ++ch) nv[ch] = v[ch];
-        for (int k = 1; k < 64; ++k) {
-            if (__ballot(active != 0) == 0ull) break;
-            nx = from_next(nx);
-            ny = from_next(ny);
-            nz = from_next(nz);
-            nval = from_next(nval);
-            nc.fx = from_next(nc.fx);
-            nc.fy = from_next(nc.fy);
-            nc.fz = from_next(nc.fz);
-#pragma unroll
-            for (int ch = 0; ch < NC; ++ch) nv[ch] = from_next(nv[ch]);
-            const bool nvalid = nval != 0;
-#pragma unroll
-            for (int cc = 0; cc < CG; ++cc) {
-                if (!(active & (1u << cc))) continue;
-                const int c = c0 + cc;
-                const int ax = cl.ix + ((c >> 2) & 1) - nx, ay = cl.iy + ((c >> 1) & 1) - ny,
-                          az = cl.iz + (c & 1) - nz;
-                if (nvalid && (unsigned)ax <= 1u && (unsigned)ay <= 1u && (unsigned)az <= 1u) {
-                    const float w = corner_weight(nc, ax, ay, az);
-#pragma unroll
-                    for (int ch = 0; ch < NC; ++ch) acc[cc][ch] += w * nv[ch];
-                } else {
-                    active &= ~(1u << cc);
-                }
-            }
-        }
-        if (NC == 1) {
-#pragma unroll
-            for (int cc = 0; cc < CG; ++cc) {
-                const int c = c0 + cc;
-                if (head & (1u << cc))
-                    unsafeAtomicAdd(g.grad + base + ((c >> 2) & 1) * g.sx + ((c >> 1) & 1) * g.sy + (c & 1) * g.cs,
-                                    acc[cc][0]);
-            }
-            continue;
-        }
-        // Multi-channel: compact the heads through this wave's LDS slice and issue the atomics with
-        // consecutive lanes on consecutive channels of one vertex, so one instruction covers a few
-        // whole vertex rows instead of one float of 64 vertices.  The two corners of a cell that
-        // differ only in z (2p, 2p + 1) are adjacent rows of the z-fastest layout: a lane puts both
-        // of its records next to each other, so a pair that both lanes' runs start on leaves as one
-        // contiguous 2C-float span (fewer memory packets per vertex than two separate rows).
-        extern __shared__ float scatter_lds[];
-        float *vals = scatter_lds + (threadIdx.x >> 6) * (128 * (NC + 1));
-        int *keys = reinterpret_cast<int *>(vals + 128 * NC);
-#pragma unroll
-        for (int pp = 0; pp < CG / 2; ++pp) {
-            const int p = c0 / 2 + pp;  // corners 2p, 2p + 1 (bits 2pp, 2pp + 1 of head)
-            const bool h0 = (head >> (2 * pp)) & 1u, h1 = (head >> (2 * pp + 1)) & 1u;
-            const unsigned long long m0 = __ballot(h0), m1 = __ballot(h1);
-            if ((m0 | m1) == 0ull) continue;
-            const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(m0 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m0, 0u)) +
-                             __builtin_amdgcn_mbcnt_hi((unsigned)(m1 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m1, 0u));
-            const int nh = __popcll(m0) + __popcll(m1);
-            const int k0 = base + ((p >> 1) & 1) * g.sx + (p & 1) * g.sy;  // corner 2p (dz = 0)
-            if (h0) {
-                keys[rank] = k0;
-#pragma unroll
-                for (int ch = 0; ch < NC; ++ch) vals[rank * NC + ch] = acc[2 * pp][ch];
-            }
-            if (h1) {
-                const int r1 = rank + (h0 ? 1 : 0);
-                keys[r1] = k0 + g.cs;
-#pragma unroll
-                for (int ch = 0; ch < NC; ++ch) vals[r1 * NC + ch] = acc[2 * pp + 1][ch];
-            }
-            lds_fence();  // the slice is this wave's own: LDS order only, the atomics stay in flight
-            for (int i = ln; i < nh * NC; i += 64) {
-                const int e = i / NC, ch = i - e * NC;
-                if (ch < nch) unsafeAtomicAdd(g.grad + keys[e] + ch, vals[i]);
-            }
-            lds_fence();
+        for (int s = 0; s < SL; ++s) {
+            cur[s] = 0;
+            acc[s] = 0.f;
         }
     }
-}
+    // fraction weight and vertex offset of parity class p on one axis
+    static __device__ __forceinline__ void axis(float tagged, int p, int stride, float &w, int &off) {
+        const int bits = __builtin_bit_cast(int, tagged);
+        const float f = __builtin_bit_cast(float, bits & 0x7fffffff);
+        const bool up = (bits < 0) != (p != 0);  // the cell's vertex of this class is its upper one
+        w = up ? f : 1.f - f;
+        off = up ? stride : 0;
+    }
+    // one sample: its staged cell and this lane's channel value; gp = grad + ch
+    __device__ __forceinline__ void step(const DevGrid &g, float *gp, const float4 &rec, float v) {
+        float wx[2], wy[2], wz;
+        int ox[2], oy[2], oz;
+        axis(rec.w, hi & 1, g.cs, wz, oz);
+        if (SL < 4) {
+            axis(rec.z, (hi >> 1) & 1, g.sy, wy[0], oy[0]);
+        } else {
+            axis(rec.z, 0, g.sy, wy[0], oy[0]);
+            axis(rec.z, 1, g.sy, wy[1], oy[1]);
+        }
+        if (SL < 2) {
+            axis(rec.y, (hi >> 2) & 1, g.sx, wx[0], ox[0]);
+        } else {
+            axis(rec.y, 0, g.sx, wx[0], ox[0]);
+            axis(rec.y, 1, g.sx, wx[1], ox[1]);
+        }
+        const int base = __builtin_bit_cast(int, rec.x) + oz;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const int ix = s & 1, iy = s >> 1;
+            const int at = base + ox[ix] + oy[iy];
+            const float w = (wx[ix] * wy[iy]) * wz;
+            if (at != cur[s]) {
+                if (acc[s] != 0.f) unsafeAtomicAdd(gp + cur[s], acc[s]);
+                cur[s] = at;
+                acc[s] = w * v;
+            } else {
+                acc[s] = __builtin_fmaf(w, v, acc[s]);
+            }
+        }
+    }
+    __device__ __forceinline__ void finish(float *gp) {
+#pragma unroll
+        for (int s = 0; s < SL; ++s)
+            if (acc[s] != 0.f) unsafeAtomicAdd(gp + cur[s], acc[s]);
+    }
+};
 
-// bytes of dynamic LDS a block of `threads` needs for scatter_wave<NC>
-__host__ __device__ constexpr int scatter_lds_bytes(int NC, int threads) {
-    return NC == 1 ? 0 : (threads / 64) * 128 * (NC + 1) * 4;
+// The slot walk over one chunk of at most 64 samples of a wave: lane l holds sample l (the first n
+// are real), its cell and its value; channel c of sample l takes val scaled by f0, f1, f2.  rec and
+// vals: this wave's LDS (64 entries each).  All lanes must call it.
+template <int NC, int SL>
+__device__ __forceinline__ void walk_chunk(const DevGrid &g, int n, const Cell &cl, float val, float f0, float f1,
+                                           float f2, float4 *rec, float *vals) {
+    static_assert(NC <= 3, "three scale factors");
+    using Walk = SlotWalk<NC, SL>;
+    constexpr int T = (64 + Walk::NG - 1) / Walk::NG;  // samples of a group
+    const int ln = lane();
+    rec[ln] = stage_cell(g, cl);
+    vals[ln] = val;
+    lds_fence();
+    Walk wk;
+    const int b = wk.group * T;
+    const int cnt = wk.group < Walk::NG ? min(min(n, 64) - b, T) : 0;
+    const float fc = wk.ch == 0 ? f0 : (wk.ch == 1 ? f1 : f2);
+    float *gp = g.grad + wk.ch;
+    for (int t = 0; t < cnt; ++t) wk.step(g, gp, rec[b + t], vals[b + t] * fc);
+    wk.finish(gp);
+    lds_fence();
 }
+constexpr int WALK_LDS_PER_WAVE = 64 * 20;  // bytes walk_chunk needs for each wave of a block
 
 __device__ __forceinline__ Tri tri_from_cell(const DevGrid &g, const Cell &c) {
     Tri t;
@@ -364,11 +335,6 @@ __device__ __forceinline__ float interp_ch(const DevGrid &g, const Tri &t, int c
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc += t.w[c] * g.data[t.base + corner_off(g, c) + ch];
     return acc;
-}
-
-__device__ __forceinline__ void scatter_ch(const DevGrid &g, const Tri &t, int ch, float v) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) unsafeAtomicAdd(&g.grad[t.base + corner_off(g, c) + ch], t.w[c] * v);
 }
 
 // ------------------------------------------------------------------------------ Adam

@@ -162,57 +162,69 @@ void launch_gather_groups(const DevGrid &dg, int64_t S, const float *xyz, float 
                            out, vec_out);
 }
 
-// One lane per sample, 64 consecutive samples per wave: consecutive samples lie along a
-// ray, so contributions to shared vertices are summed in the wave before the atomics.
-template <int NC, bool W>
+// Scatter by slot walks (SlotWalk): each group of lanes walks L consecutive samples, NG groups per
+// wave, in rounds of up to T samples per group.  A round first stages its cells (one lane per
+// sample) and its gradient rows (contiguous per group) in LDS, so that the walk itself waits for no
+// memory: on gfx950 loads and atomics share one in-order counter, and a load inside the walk would wait
+// for every atomic before it.
+template <int NC, int SL, bool W>
 __global__ __launch_bounds__(kBlock) void scatter_kernel(DevGrid g, int64_t S, const float *__restrict__ xyz,
-                                                         const float *__restrict__ gout, int vec_in) {
-    const int64_t nwaves = (int64_t)gridDim.x * (kBlock / 64);
-    const int64_t wave = (blockIdx.x * (int64_t)kBlock + threadIdx.x) >> 6;
-    for (int64_t base = wave * 64; base < S; base += nwaves * 64) {
-        const int64_t k = base + lane();
-        const bool valid = k < S;
-        Cell cl{0, 0, 0, 0.f, 0.f, 0.f};
-        float v[NC];
+                                                         const float *__restrict__ gout, int L) {
+    using Walk = SlotWalk<NC, SL>;
+    constexpr int NG = Walk::NG, T = 64 / NG;
+    __shared__ float4 recs[kBlock / 64][NG * T];
+    __shared__ float rows[kBlock / 64][NG * T * NC];
+    const int wv = threadIdx.x >> 6, ln = lane();
+    float4 *rec = recs[wv];
+    float *row = rows[wv];
+    const int64_t first = (blockIdx.x * (int64_t)(kBlock / 64) + wv) * NG * L;  // the wave's first sample
+    if (first >= S) return;
+    Walk wk;
+    const int sg = ln / T, si = ln - sg * T;  // the group and step this lane stages a cell for
+    float *gp = g.grad + wk.ch;
+    for (int r = 0; r < L; r += T) {
+        const int n = min(T, L - r);  // steps of this round
+        const int64_t ks = first + (int64_t)sg * L + r + si;
+        if (sg < NG && si < n && ks < S)
+            rec[ln] = stage_cell(g, cell_of<W>(g, xyz[3 * ks], xyz[3 * ks + 1], xyz[3 * ks + 2]));
 #pragma unroll
-        for (int ch = 0; ch < NC; ++ch) v[ch] = 0.f;
-        if (valid) {
-            cl = cell_of<W>(g, xyz[3 * k], xyz[3 * k + 1], xyz[3 * k + 2]);
-            if (NC % 4 == 0 && vec_in) {
-                // C % 4 == 0 and gout 16-byte aligned: the row arrives as C / 4 float4 loads
+        for (int h = 0; h < NG; ++h) {
+            const int64_t k0 = first + (int64_t)h * L + r;
+            const int nf = (int)(k0 >= S ? 0 : (S - k0 < n ? S - k0 : n)) * g.C;
+            const float *src = gout + k0 * g.C;
 #pragma unroll
-                for (int q = 0; q < NC / 4; ++q)
-                    if (4 * q < g.C) {
-                        const float4 t = *reinterpret_cast<const float4 *>(gout + k * g.C + 4 * q);
-                        v[4 * q] = t.x;
-                        v[4 * q + 1] = t.y;
-                        v[4 * q + 2] = t.z;
-                        v[4 * q + 3] = t.w;
-                    }
-            } else {
-#pragma unroll
-                for (int ch = 0; ch < NC; ++ch)
-                    if (ch < g.C) v[ch] = gout[k * g.C + ch];
-            }
+            for (int i = 0; i < T * NC; i += 64)
+                if (i + ln < nf) row[h * T * NC + i + ln] = src[i + ln];
         }
-        scatter_wave<NC>(g, valid, cl, v, g.C);
+        lds_fence();
+        const int64_t left = S - (first + (int64_t)wk.group * L + r);
+        const int cnt = wk.group >= NG || wk.ch >= g.C || left <= 0 ? 0 : (left < n ? (int)left : n);
+        const float4 *rp = rec + wk.group * T;
+        const float *vp = row + wk.group * T * NC + wk.ch;
+        for (int t = 0; t < cnt; ++t) wk.step(g, gp, rp[t], vp[t * g.C]);
+        lds_fence();
     }
+    wk.finish(gp);
 }
 
 // rows of C floats can move as float4: C % 4 == 0 and the array 16-byte aligned
 inline int vec_rows(const float *p, int C) { return (C & 3) == 0 && ((uintptr_t)p & 15) == 0 ? 1 : 0; }
 
-template <int NC>
+// Run length: long runs save the eight vertices that every run's end sends out early, short ones give
+// the chip more waves.  Runs grow with S until about 2048 waves are busy twice over, in whole rounds up
+// to four (longer ones gained nothing: 193 us at four rounds, 214 at eight, 12 channels, 981,504 samples);
+// no run is shorter than 8 (one channel: 16) samples (7,488 samples: 10 us at any length from 2 to 16).
+template <int NC, int SL>
 void launch_scatter(const DevGrid &dg, int64_t S, const float *xyz, const float *gout, hipStream_t st) {
-    int64_t waves = (S + 63) / 64;
-    int64_t blocks = (waves + 3) / 4;
-    if (blocks > 256 * 16) blocks = 256 * 16;
+    constexpr int NG = SlotWalk<NC, SL>::NG, T = 64 / NG, LMIN = NC == 1 ? 16 : 8, LMAX = 4 * T;
+    const int64_t len = S / ((int64_t)NG * 2048);
+    const int L = (int)(len < LMIN ? LMIN : (len > LMAX ? LMAX : (len < T ? len : len / T * T)));
+    const int64_t waves = (S + (int64_t)NG * L - 1) / ((int64_t)NG * L);
+    const unsigned blocks = (unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64));
     if (dg.warp)
-        hipLaunchKernelGGL((scatter_kernel<NC, true>), dim3((unsigned)blocks), dim3(kBlock),
-                           scatter_lds_bytes(NC, kBlock), st, dg, S, xyz, gout, vec_rows(gout, dg.C));
+        hipLaunchKernelGGL((scatter_kernel<NC, SL, true>), dim3(blocks), dim3(kBlock), 0, st, dg, S, xyz, gout, L);
     else
-        hipLaunchKernelGGL((scatter_kernel<NC, false>), dim3((unsigned)blocks), dim3(kBlock),
-                           scatter_lds_bytes(NC, kBlock), st, dg, S, xyz, gout, vec_rows(gout, dg.C));
+        hipLaunchKernelGGL((scatter_kernel<NC, SL, false>), dim3(blocks), dim3(kBlock), 0, st, dg, S, xyz, gout, L);
 }
 
 template <bool W>
@@ -382,12 +394,12 @@ extern "C" int dvgo_grid_scatter(const dvgo_grid *g, int64_t n_samples, const fl
     if (!xyz || !grad_out) return set_error(DVGO_ERR_NULL, "xyz or grad_out is NULL");
     const hipStream_t st = (hipStream_t)stream;
     const int C = g->channels;
-    if (C == 1) launch_scatter<1>(dg, n_samples, xyz, grad_out, st);
-    else if (C <= 3) launch_scatter<3>(dg, n_samples, xyz, grad_out, st);
-    else if (C <= 4) launch_scatter<4>(dg, n_samples, xyz, grad_out, st);
-    else if (C <= 8) launch_scatter<8>(dg, n_samples, xyz, grad_out, st);
-    else if (C <= 12) launch_scatter<12>(dg, n_samples, xyz, grad_out, st);
-    else launch_scatter<16>(dg, n_samples, xyz, grad_out, st);
+    if (C == 1) launch_scatter<1, 1>(dg, n_samples, xyz, grad_out, st);
+    else if (C <= 3) launch_scatter<3, 2>(dg, n_samples, xyz, grad_out, st);
+    else if (C <= 4) launch_scatter<4, 4>(dg, n_samples, xyz, grad_out, st);
+    else if (C <= 8) launch_scatter<8, 4>(dg, n_samples, xyz, grad_out, st);
+    else if (C <= 12) launch_scatter<12, 4>(dg, n_samples, xyz, grad_out, st);
+    else launch_scatter<16, 4>(dg, n_samples, xyz, grad_out, st);
     return check_hip(hipGetLastError(), "scatter_kernel launch");
 }
 
