@@ -128,7 +128,8 @@ __device__ __forceinline__ void warped_coords(const DevGrid &g, float x, float y
     } else {
         n = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2]);
     }
-    const double s = n > 1.0 ? (1.0 + g.wb - g.wb / n) / n : 1.0;
+    const double r = 1.0 / n;  // the one division of the contraction
+    const double s = n > 1.0 ? (1.0 + g.wb - g.wb * r) * r : 1.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const double u = p[a] * s * g.s_d[a] + g.o_d[a];
@@ -201,23 +202,35 @@ __device__ __forceinline__ void lds_fence() { __builtin_amdgcn_fence(__ATOMIC_AC
 // consecutive channels and those of the two z parities follow each other, so vertices of one column
 // that leave together leave as one contiguous span.  64 / GL groups per wave walk side by side.
 //
-// The samples' cells are staged in LDS first, one lane per sample (stage_cell): the float index of
-// the cell's low corner and the three fractions, each with the parity of its cell index in the
-// (otherwise clear) sign bit.
-__device__ __forceinline__ float4 stage_cell(const DevGrid &g, const Cell &c) {
+// A sample's cell is a float4 (stage_cell): the offset of the cell's low corner and the three
+// fractions, each with the parity of its cell index in the (otherwise clear) sign bit.  Where a group
+// has more than one lane the cells are staged in LDS, one lane per sample.
+__device__ __forceinline__ float4 stage_cell(int low, const Cell &c) {
     const auto tag = [](float f, int i) {
         return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, f) & 0x7fffffffu) | ((unsigned)i << 31));
     };
-    return make_float4(__builtin_bit_cast(float, c.ix * g.sx + c.iy * g.sy + c.iz * g.cs), tag(c.fx, c.ix),
-                       tag(c.fy, c.iy), tag(c.fz, c.iz));
+    return make_float4(__builtin_bit_cast(float, low), tag(c.fx, c.ix), tag(c.fy, c.iy), tag(c.fz, c.iz));
 }
+__device__ __forceinline__ float4 stage_cell(const DevGrid &g, const Cell &c) {
+    return stage_cell(c.ix * g.sx + c.iy * g.sy + c.iz * g.cs, c);
+}
+
+// where a finished vertex sum goes: base[offset] in global memory or in LDS
+struct GlobalSum {
+    float *base;
+    __device__ __forceinline__ void operator()(int at, float v) const { unsafeAtomicAdd(base + at, v); }
+};
+struct LdsSum {
+    float *base;
+    __device__ __forceinline__ void operator()(int at, float v) const { atomicAdd(base + at, v); }
+};
 
 template <int NC, int SL>
 struct SlotWalk {
     static constexpr int GL = (8 / SL) * NC;  // lanes of a group
     static constexpr int NG = 64 / GL;        // groups of a wave
-    static_assert(GL <= 64 && (SL == 1 || SL == 2 || SL == 4), "a group fits a wave");
-    int cur[SL];    // float offset (without the channel) of the vertex each slot holds
+    static_assert(GL <= 64 && (SL == 1 || SL == 2 || SL == 4 || SL == 8), "a group fits a wave");
+    int cur[SL];    // offset (without the channel) of the vertex each slot holds
     float acc[SL];  // its sum so far; 0 when nothing is held
     int group, ch, hi;
 
@@ -240,31 +253,26 @@ struct SlotWalk {
         w = up ? f : 1.f - f;
         off = up ? stride : 0;
     }
-    // one sample: its staged cell and this lane's channel value; gp = grad + ch
-    __device__ __forceinline__ void step(const DevGrid &g, float *gp, const float4 &rec, float v) {
-        float wx[2], wy[2], wz;
-        int ox[2], oy[2], oz;
-        axis(rec.w, hi & 1, g.cs, wz, oz);
-        if (SL < 4) {
-            axis(rec.z, (hi >> 1) & 1, g.sy, wy[0], oy[0]);
-        } else {
-            axis(rec.z, 0, g.sy, wy[0], oy[0]);
-            axis(rec.z, 1, g.sy, wy[1], oy[1]);
-        }
-        if (SL < 2) {
-            axis(rec.y, (hi >> 2) & 1, g.sx, wx[0], ox[0]);
-        } else {
-            axis(rec.y, 0, g.sx, wx[0], ox[0]);
-            axis(rec.y, 1, g.sx, wx[1], ox[1]);
-        }
-        const int base = __builtin_bit_cast(int, rec.x) + oz;
+    // one sample: its cell and this lane's channel value; sx, sy, sz: vertex strides of the target
+    template <class Sum>
+    __device__ __forceinline__ void step(int sx, int sy, int sz, const float4 &rec, float v, const Sum &sum) {
+        constexpr int NX = SL > 1 ? 2 : 1, NY = SL > 2 ? 2 : 1, NZ = SL > 4 ? 2 : 1;  // classes in registers
+        float wx[NX], wy[NY], wz[NZ];
+        int ox[NX], oy[NY], oz[NZ];
+#pragma unroll
+        for (int p = 0; p < NX; ++p) axis(rec.y, NX > 1 ? p : (hi >> 2) & 1, sx, wx[p], ox[p]);
+#pragma unroll
+        for (int p = 0; p < NY; ++p) axis(rec.z, NY > 1 ? p : (hi >> 1) & 1, sy, wy[p], oy[p]);
+#pragma unroll
+        for (int p = 0; p < NZ; ++p) axis(rec.w, NZ > 1 ? p : hi & 1, sz, wz[p], oz[p]);
+        const int base = __builtin_bit_cast(int, rec.x);
 #pragma unroll
         for (int s = 0; s < SL; ++s) {
-            const int ix = s & 1, iy = s >> 1;
-            const int at = base + ox[ix] + oy[iy];
-            const float w = (wx[ix] * wy[iy]) * wz;
+            const int ix = s & 1, iy = (s >> 1) & 1, iz = s >> 2;
+            const int at = base + ox[ix] + oy[iy] + oz[iz];
+            const float w = (wx[ix] * wy[iy]) * wz[iz];
             if (at != cur[s]) {
-                if (acc[s] != 0.f) unsafeAtomicAdd(gp + cur[s], acc[s]);
+                if (acc[s] != 0.f) sum(cur[s], acc[s]);
                 cur[s] = at;
                 acc[s] = w * v;
             } else {
@@ -272,10 +280,11 @@ struct SlotWalk {
             }
         }
     }
-    __device__ __forceinline__ void finish(float *gp) {
+    template <class Sum>
+    __device__ __forceinline__ void finish(const Sum &sum) {
 #pragma unroll
         for (int s = 0; s < SL; ++s)
-            if (acc[s] != 0.f) unsafeAtomicAdd(gp + cur[s], acc[s]);
+            if (acc[s] != 0.f) sum(cur[s], acc[s]);
     }
 };
 
@@ -296,9 +305,9 @@ __device__ __forceinline__ void walk_chunk(const DevGrid &g, int n, const Cell &
     const int b = wk.group * T;
     const int cnt = wk.group < Walk::NG ? min(min(n, 64) - b, T) : 0;
     const float fc = wk.ch == 0 ? f0 : (wk.ch == 1 ? f1 : f2);
-    float *gp = g.grad + wk.ch;
-    for (int t = 0; t < cnt; ++t) wk.step(g, gp, rec[b + t], vals[b + t] * fc);
-    wk.finish(gp);
+    const GlobalSum sum{g.grad + wk.ch};
+    for (int t = 0; t < cnt; ++t) wk.step(g.sx, g.sy, g.cs, rec[b + t], vals[b + t] * fc, sum);
+    wk.finish(sum);
     lds_fence();
 }
 constexpr int WALK_LDS_PER_WAVE = 64 * 20;  // bytes walk_chunk needs for each wave of a block

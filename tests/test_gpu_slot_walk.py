@@ -38,3 +38,25 @@ def test_slot_walk_edges(C, cs, S):
     want = before[..., :C].astype(np.float64) + oracle.scatter(g, xyz, y.astype(np.float64)).reshape(n, n, n, C)
     close(got[..., :C], want, **GRAD, name="scatter")
     assert np.array_equal(got[..., C:], before[..., C:])
+
+
+@pytest.mark.parametrize("n,S,crowd", [(9, 64, 0), (9, 65, 0), (40, 3000, 0), (40, 3000, 2500), (180, 20001, 6000)])
+def test_binned_scatter_crowded_bricks(n, S, crowd):
+    # bricks of at most 64 samples (one wave, global atomics) beside crowded ones (the block's LDS tile),
+    # one and several bricks per block, more than one block of the prefix sum (180^3: 12,167 bricks)
+    from paper_2206_05085_amd import ops
+    rng = np.random.default_rng(n + S)
+    g = synth.normal_grid(rng, n, 1)
+    xyz = rng.uniform(-1.05, 1.05, (S, 3)).astype(np.float32)
+    if crowd:
+        xyz[:crowd] = (0.31 + 0.0007 * np.arange(crowd)[:, None] * rng.uniform(-0.1, 0.1, 3)).astype(np.float32)
+    y = rng.standard_normal((S, 1)).astype(np.float32)
+    print(f"[case] crowded bricks n={n} S={S} crowd={crowd}", flush=True)
+    dg = ops.DeviceGrid(torch.from_numpy(g.data).cuda(), g.xyz_min, g.xyz_max,
+                        grad=torch.zeros(n, n, n, 1, device="cuda"))
+    t = torch.from_numpy(xyz).cuda()
+    ws = ops.bin_samples(dg, t)
+    for _ in range(2):  # the bins serve several scatters
+        ops.grid_scatter_binned(dg, t, torch.from_numpy(y).cuda(), ws)
+    torch.cuda.synchronize()
+    close(dg.grad.cpu().numpy(), 2.0 * oracle.scatter(g, xyz, y.astype(np.float64)), **GRAD, name="binned scatter")
