@@ -42,6 +42,7 @@ typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 constexpr int H = 128;      // hidden width
 constexpr int KX = 64;      // padded input width: features 0..11, view encoding 12..47, zeros 48..63
 constexpr int PEW = 36;     // per-ray encoding row (input columns 12..47)
+constexpr int RBW = H + 4;  // per-ray layer-1 bias row: H biases, their largest magnitude, padding
 constexpr int RS1 = 72;     // row stride (halves) of a 64-wide operand row
 constexpr int RS2 = 136;    // row stride (halves) of a 128-wide operand row
 constexpr int MAXE = 100;   // clamp of scaling exponents
@@ -72,7 +73,8 @@ struct Meta {
     int sw1, sw2;           // weight exponents of W1 and W2 (W2^T shares sw2, W1F shares sw1)
     float n1, b1max;        // max_i sum_k |W1[i][k]|, max |b1|
     float n2t, n3t;         // max_in sum_out |W2[out][in]|, max_h sum_o |W3[o][h]|
-    int pad[6];
+    float n1f;              // max_i sum over the feature columns k of |W1[i][k]|
+    int pad[5];
 };
 static_assert(sizeof(Meta) == 48, "meta size");
 
@@ -180,6 +182,7 @@ struct MlpArgs {
     float *rgb;
     unsigned char *img;  // weight image (workspace)
     float *pe;           // [R][PEW] view encodings (workspace)
+    float *rb;           // [R][RBW] layer-1 biases of the rays, b1 + W1 (view encoding), and their largest magnitude
     int *tile_ray;       // [ceil(S/32)] ray of the first sample of each 32-sample tile (workspace)
     int n_tiles;         // ceil(S/32)
     const float *grad_rgb;
@@ -216,24 +219,8 @@ __device__ __forceinline__ int find_ray(const int *offs, int R, int s) {
     return lo;
 }
 
-// The same search for a sample of the 32-sample tile whose first sample lies on ray r0:
-// every lane of the wave holds w = offs[min(r0 + lane, R)] and the search runs over the
-// 64-entry window with shuffles; a sample beyond the window falls back to find_ray.  All
-// 64 lanes must call it (the shuffles read every lane).
-__device__ __forceinline__ int ray_in_window(const int *offs, int R, int r0, int w, int s) {
-    int lo = 0, hi = 63;
-#pragma unroll
-    for (int it = 0; it < 6; ++it) {
-        const int mid = (lo + hi + 1) >> 1;
-        const int v = __shfl(w, mid, 64);
-        if (v <= s) lo = mid; else hi = mid - 1;
-    }
-    if (lo == 63 && r0 + 64 <= R && offs[r0 + 64] <= s) return find_ray(offs, R, s);
-    return r0 + lo;
-}
-
-// The same ray for the 8 consecutive samples sbase + (lane >> 3) of a wave (sbase wave-uniform
-// and at or after offs[r0]): per sample, a ballot counts the window entries at or before it
+// The ray of each of the 8 consecutive samples sbase + (lane >> 3) of a wave (sbase wave-uniform and
+// at or after offs[r0]), where lane l holds w = offs[min(r0 + l, R)]: per sample, a ballot counts the window entries at or before it
 // (a prefix, as offs is non-decreasing), so no lane-to-lane round trips are needed.  All 64
 // lanes must call it.
 __device__ __forceinline__ int ray_of_group8(const int *offs, int R, int r0, int w, int sbase) {
@@ -283,20 +270,24 @@ constexpr int PREP_FIXED_BLOCKS = PREP_W2_BLOCKS + PREP_W1_BLOCKS + 1;
 // blocks [0, 16): W2 and W2^T planes; every one of them also reduces max|W2| and the column
 // sums of |W2| from the same loads (block 0 stores sw2 and n2t).  Blocks [16, 20): W1 planes,
 // max|W1| and the row sums of |W1| (block 16 stores sw1, n1, b1max and writes W1F, b1, b3).
-// Block 20: W3, b2, n3t.  Then view encodings (one ray per thread) and tile start rays.
+// Block 20: W3, b2, n3t.  Then the rays (PREP_RAYS per block: view encodings, one entry per thread, and
+// the layer-1 biases that follow from them, one unit per thread) and the tile start rays.
+constexpr int PREP_RAYS = 16;
 __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
     __shared__ float red[PREP_THREADS / 64];
     __shared__ float sums[PREP_THREADS];
+    __shared__ float enc[PREP_RAYS][PEW];
+    __shared__ float w1[H * 39];  // the ray blocks' copy of W1 (at most 39 columns)
     unsigned char *img = a.img;
     Meta *meta = reinterpret_cast<Meta *>(img + IMG_META);
     const int tid = threadIdx.x, b = blockIdx.x;
-    const int pe_blocks = (a.n_rays + PREP_THREADS - 1) / PREP_THREADS;
+    const int pe_blocks = (a.n_rays + PREP_RAYS - 1) / PREP_RAYS;
     if (b < PREP_W2_BLOCKS) {
         // element i = tid + 512 k sits in column tid % 128 (512 is a multiple of H)
         float m = 0.f, cs = 0.f;
-#pragma unroll 8
-        for (int i = tid; i < H * H; i += PREP_THREADS) {
-            const float v = fabsf(a.W2[i]);
+#pragma unroll
+        for (int i = 0; i < H * H / PREP_THREADS; ++i) {  // all the loads in flight at once
+            const float v = fabsf(a.W2[tid + i * PREP_THREADS]);
             m = fmaxf(m, v);
             cs += v;
         }
@@ -320,14 +311,22 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
         }
     } else if (b < PREP_W2_BLOCKS + PREP_W1_BLOCKS) {
         const int wb = b - PREP_W2_BLOCKS;
-        if (tid < H) sums[tid] = 0.f;
-        __syncthreads();
-        float m = 0.f;
-        for (int i = tid; i < H * a.n_in; i += PREP_THREADS) {
-            const float v = fabsf(a.W1[i]);
+        // four threads per row, every fourth column each: the row sums of |W1| over all columns and over the
+        // feature columns
+        float m = 0.f, all = 0.f, fs = 0.f;
+        const int row = tid >> 2;
+#pragma unroll
+        for (int i = 0; i < 10; ++i) {  // at most 39 columns
+            const int c = (tid & 3) + 4 * i;
+            const float v = c < a.n_in ? fabsf(a.W1[row * a.n_in + c]) : 0.f;
             m = fmaxf(m, v);
-            atomicAdd(&sums[i / a.n_in], v);
+            all += v;
+            fs += c < a.in_feat ? v : 0.f;
         }
+        all += __shfl_xor(all, 1, 64);
+        fs += __shfl_xor(fs, 1, 64);
+        all += __shfl_xor(all, 2, 64);
+        fs += __shfl_xor(fs, 2, 64);
         const int sw = scale_exp(block_max(m, red));
         const float sc = pow2(sw);
         for (int i = tid; i < 32 * RS1; i += PREP_THREADS) {
@@ -336,7 +335,7 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
             put_split(img, IMG_W1H, IMG_W1L, row * RS1 + p, c >= 0 ? a.W1[row * a.n_in + c] : 0.f, sc);
         }
         if (wb == 0) {
-            const float n1 = block_max(tid < H ? sums[tid] : 0.f, red);
+            const float n1 = block_max(all, red), n1f = block_max(fs, red);
             const float b1max = block_max(tid < H ? fabsf(a.b1[tid]) : 0.f, red);
             // W1F[c][phys over hidden] = W1[hidden][c] for the feature columns c < in_feat
             for (int i = tid; i < 16 * RS2; i += PREP_THREADS) {
@@ -351,6 +350,7 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
             if (tid == 0) {
                 meta->sw1 = sw;
                 meta->n1 = n1;
+                meta->n1f = n1f;
                 meta->b1max = b1max;
             }
         }
@@ -369,18 +369,54 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
         const int t = (b - PREP_FIXED_BLOCKS - pe_blocks) * PREP_THREADS + tid;
         if (t < a.n_tiles) a.tile_ray[t] = find_ray(a.offs, a.n_rays, TILE * t);
     } else {
-        const int r = (b - PREP_FIXED_BLOCKS) * PREP_THREADS + tid;
-        if (r < a.n_rays) {
-            const float d[3] = {a.dirs[3 * r], a.dirs[3 * r + 1], a.dirs[3 * r + 2]};
-            float *row = a.pe + (int64_t)r * PEW;
-            for (int i = 0; i < PEW; ++i) row[i] = 0.f;
-            for (int ax = 0; ax < 3; ++ax) row[ax] = d[ax];
-            for (int f = 0; f < a.n_freq; ++f)
-                for (int ax = 0; ax < 3; ++ax) {
-                    const float v = ldexpf(d[ax], f);
-                    row[3 + 3 * f + ax] = sinf(v);
-                    row[3 + 3 * a.n_freq + 3 * f + ax] = cosf(v);
-                }
+        const int r0 = (b - PREP_FIXED_BLOCKS) * PREP_RAYS, nr = min(PREP_RAYS, a.n_rays - r0), F = a.n_freq;
+        float wl[10];  // W1, read with coalesced loads before the encodings are formed
+#pragma unroll
+        for (int i = 0; i < 10; ++i) {
+            const int k = tid + i * PREP_THREADS;
+            wl[i] = k < H * a.n_in ? a.W1[k] : 0.f;
+        }
+        for (int i = tid; i < PREP_RAYS * PEW; i += PREP_THREADS) {
+            const int r = i / PEW, e = i - r * PEW;
+            float v = 0.f;
+            if (r < nr && e < 3 + 6 * F) {
+                const int q = e < 3 ? e : (e - 3) % (3 * F), ax = e < 3 ? e : q % 3;
+                const float d = a.dirs[3 * (r0 + r) + ax];
+                const float t = ldexpf(d, e < 3 ? 0 : q / 3);
+                v = e < 3 ? d : (e < 3 + 3 * F ? sinf(t) : cosf(t));
+            }
+            enc[r][e] = v;
+            if (r < nr) a.pe[(int64_t)r0 * PEW + i] = v;
+        }
+#pragma unroll
+        for (int i = 0; i < 10; ++i)
+            if (tid + i * PREP_THREADS < H * 39) w1[tid + i * PREP_THREADS] = wl[i];
+        __syncthreads();
+        const int u = tid & (H - 1), NE = 3 + 6 * F;
+        const float *w = w1 + u * a.n_in + a.in_feat;
+        const float bu = a.b1[u];
+        float acc[PREP_RAYS * H / PREP_THREADS];
+#pragma unroll
+        for (int i = 0; i < PREP_RAYS * H / PREP_THREADS; ++i) acc[i] = bu;
+        for (int e = 0; e < NE; ++e) {
+            const float we = w[e];
+#pragma unroll
+            for (int i = 0; i < PREP_RAYS * H / PREP_THREADS; ++i)
+                acc[i] = fmaf(we, enc[i * (PREP_THREADS / H) + tid / H][e], acc[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < PREP_RAYS * H / PREP_THREADS; ++i) {
+            const int r = i * (PREP_THREADS / H) + tid / H;
+            float m = fabsf(acc[i]);  // largest magnitude over the wave's 64 units, then over the ray's two waves
+            for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+            __syncthreads();
+            if (lane() == 0) red[tid >> 6] = m;
+            __syncthreads();
+            if (r < nr) {
+                float *row = a.rb + (int64_t)(r0 + r) * RBW;
+                row[u] = acc[i];
+                if (u == 0) row[H] = fmaxf(red[tid >> 6], red[(tid >> 6) + 1]);
+            }
         }
     }
 }
@@ -433,263 +469,293 @@ __device__ __forceinline__ void copy_to_lds(unsigned char *dst, const unsigned c
 
 // ------------------------------------------------------------------ forward
 //
-// The forward's LDS copy of the weight image re-strides the FP16 weight rows.  On gfx950 the
-// operand reads of a row tile (lane j reads row j, lane group q the 16 bytes at 16 q) run without
-// bank conflicts when the row stride is 32 bytes more than a multiple of 64; the image's strides
-// (272 and 144 bytes, which the backward's planes share) are 16 bytes more and read about 1.7x
-// slower (measured with this read pattern in isolation: ~120 against ~205 bytes per clock per CU).
-constexpr int FRS2 = 144;  // halves per W2 row in the forward's LDS (128 used)
-constexpr int FRS1 = 80;   // halves per W1 row in the forward's LDS (64 used)
-constexpr int F_W2H = 0;
-constexpr int F_W2L = F_W2H + H * FRS2 * 2;
-constexpr int F_W1H = F_W2L + H * FRS2 * 2;
-constexpr int F_W1L = F_W1H + H * FRS1 * 2;
-constexpr int F_SMALL = F_W1L + H * FRS1 * 2;          // b1, b2, W3, b3, meta, laid out as in the image
-constexpr int F_END = F_SMALL + (IMG_FWD_END - IMG_B1);
-static_assert((FRS2 * 2) % 64 == 32 && (FRS1 * 2) % 64 == 32 && F_SMALL % 16 == 0, "forward LDS strides");
-static_assert(F_END <= 160 * 1024, "forward LDS block");
+// Wave tiles of 32 samples x 128 units on v_mfma_f32_32x32x16_f16: lane (hf = lane / 32, j = lane % 32)
+// of a 32 x 32 accumulator tile owns units 8 i + 4 hf + r (i, r < 4) of sample j, and a K-step of 16
+// reads the lane's 8 operand slots (hf, e) as logical index 16 ks + 8 (e / 4) + 4 hf + e % 4, so a row
+// tile of one layer's output is two K-steps of the next layer's B operand without any data movement.  W1
+// and W2 sit in LDS (both parts), their columns in that slot order; three waves per SIMD (12 per block,
+// at most 168 registers).  In the split mode layer 1 multiplies the features only (one K-step): the view
+// encoding is the same for all samples of a ray, and its part of layer 1 is the ray's bias row, made once
+// per ray by the preparation.  (The FP16 mode keeps the encoding in the product, K = 48: its operands are
+// rounded, and so is its encoding.)
+//
+// Bound by the matrix and vector units together, which overlap by about half on this chip (measured: eight
+// 32 x 32 x 16 products and 56 FMAs of two waves take 188 ns where the products alone take 145 and the FMAs
+// 82), and by the clock, which falls to 1.8-1.9 GHz under them; with the lookup inside also by its loads.
+// 959,000 samples without the lookup 143 -> 105 us, 3,926,000 with it 626 -> 500-540 us.  Of that the larger
+// tiles (half the weight reads and matrix instructions of 16 x 16 x 32 tiles, K = 48 instead of 64) gave
+// 143 -> 124, the rays' bias rows and the ray search by ray starts (instead of six dependent lane
+// shuffles) 124 -> 108.
+constexpr int FRS2 = 136;  // halves per W2 row in the forward's LDS (128 used)
+constexpr int FWD_WAVES = 12, FWD_THREADS = 64 * FWD_WAVES;
 
-// rows of row_bytes (a multiple of 16) from src with stride sstride to dst with stride dstride
+// LDS row strides: a 16-byte read of 32 rows at one column runs without bank conflicts when the stride is
+// an odd multiple of 16 bytes.
+template <bool SPLIT>
+struct FwdLds {
+    static constexpr int K1 = SPLIT ? 1 : 3;         // K-steps of layer 1
+    static constexpr int RS1 = SPLIT ? 24 : 56;      // halves per W1 row
+    static constexpr int W2H = 0, W2L = W2H + H * FRS2 * 2, W1H = W2L + (SPLIT ? H * FRS2 * 2 : 0),
+                         W1L = W1H + H * RS1 * 2,
+                         SMALL = W1L + (SPLIT ? H * RS1 * 2 : 0),  // b1, b2, W3, b3, meta, laid out as in the image
+                         END = SMALL + (IMG_FWD_END - IMG_B1);
+    static_assert((FRS2 * 2) % 32 == 16 && (RS1 * 2) % 32 == 16 && SMALL % 16 == 0 && END <= 160 * 1024, "strides");
+};
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ v16f mfma32(h8 a, h8 b, v16f c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// Copies the first 4 * GROUPS columns of the image's weight rows (stride sstride bytes) to LDS, from the
+// image's slot order to the forward's: both keep groups of four consecutive columns together, column
+// group u (columns 4 u ..) at group 8 (u / 8) + 2 (u % 4) + (u / 4) % 2 there and at 4 (u / 4) + 2 (u % 2)
+// + (u / 2) % 2 here.
+template <int GROUPS>
 __device__ __forceinline__ void copy_rows_to_lds(unsigned char *dst, int dstride, const unsigned char *src,
-                                                 int sstride, int rows, int row_bytes) {
-    const int chunks = row_bytes / 16;
-    for (int i = threadIdx.x; i < rows * chunks; i += blockDim.x) {
-        const int r = i / chunks, c = i - r * chunks;
-        *reinterpret_cast<uint4 *>(dst + r * dstride + 16 * c) =
-            *reinterpret_cast<const uint4 *>(src + r * sstride + 16 * c);
+                                                 int sstride) {
+    for (int i = threadIdx.x; i < H * GROUPS; i += FWD_THREADS) {
+        const int r = i / GROUPS, u = i - r * GROUPS;
+        const int from = 8 * (u >> 3) + 2 * (u & 3) + ((u >> 2) & 1), to = 4 * (u >> 2) + 2 * (u & 1) + ((u >> 1) & 1);
+        *reinterpret_cast<uint2 *>(dst + r * dstride + 8 * to) =
+            *reinterpret_cast<const uint2 *>(src + r * sstride + 8 * from);
     }
 }
 
-// Wave tiles of the forward: with the feature lookup inside (GM > 0) 16 samples per wave and 16
-// waves per block, so four waves share each SIMD and hide the lookups' latency behind each other's
-// products; with the features read from memory 32 samples per wave and 8 waves, which reuses each
-// weight operand for two column tiles.
-template <int GM>
-struct FwdShape {
-    static constexpr int NC = GM ? 1 : 2;       // 16-sample column tiles per wave tile
-    static constexpr int WAVES = GM ? 16 : 8;   // waves per block
-    static constexpr int THREADS = 64 * WAVES;
-    static constexpr int WTILE = 16 * NC;       // samples per wave tile
-    static_assert(TILE % WTILE == 0, "forward wave tiles split the 32-sample tiles of tile_ray");
-};
+// the value of the lane of the other half of the wave (lane l of lane l + 32 and the other way round)
+__device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32, 64); }
+
+// The ray of sample s of the 32-sample tile whose first sample lies on ray r0, where lane l holds w =
+// offs[min(r0 + l, R)]: only rays with samples matter, and those that start inside the tile are few, so
+// they are taken one by one (wave-uniform).  All 64 lanes must call it.
+__device__ __forceinline__ int ray_in_tile(const int *offs, int R, int r0, int w, int tile0, int s) {
+    const int after = __shfl_down(w, 1, 64);
+    const bool starts = lane() < 63 && w > tile0 && w < tile0 + TILE && after > w;
+    int ray = r0;
+    for (unsigned long long b = __ballot(starts); b; b &= b - 1) {
+        const int l = __ffsll((long long)b) - 1;
+        if (s >= __builtin_amdgcn_readlane(w, l)) ray = r0 + l;
+    }
+    // the window's last entry: a ray whose end is not in it, or a later one
+    if (s >= __builtin_amdgcn_readlane(w, 63)) ray = find_ray(offs, R, s);
+    return ray;
+}
 
 template <bool SPLIT, int GM>
-__global__ __launch_bounds__(FwdShape<GM>::THREADS) void mlp_fwd_kernel(MlpArgs a) {
-    constexpr int FWD_NC = FwdShape<GM>::NC, FWD_WAVES = FwdShape<GM>::WAVES, FWD_WTILE = FwdShape<GM>::WTILE;
-    __shared__ __attribute__((aligned(16))) unsigned char sm[F_END];
-    copy_rows_to_lds(sm + F_W2H, FRS2 * 2, a.img + IMG_W2H, RS2 * 2, H, H * 2);
-    copy_rows_to_lds(sm + F_W2L, FRS2 * 2, a.img + IMG_W2L, RS2 * 2, H, H * 2);
-    copy_rows_to_lds(sm + F_W1H, FRS1 * 2, a.img + IMG_W1H, RS1 * 2, H, 64 * 2);
-    copy_rows_to_lds(sm + F_W1L, FRS1 * 2, a.img + IMG_W1L, RS1 * 2, H, 64 * 2);
-    copy_to_lds(sm + F_SMALL, a.img + IMG_B1, IMG_FWD_END - IMG_B1);
+__global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
+    using L = FwdLds<SPLIT>;
+    constexpr int K1 = L::K1, FRS1 = L::RS1;
+    __shared__ __attribute__((aligned(16))) unsigned char sm[L::END];
+    copy_rows_to_lds<32>(sm + L::W2H, FRS2 * 2, a.img + IMG_W2H, RS2 * 2);
+    copy_rows_to_lds<4 * K1>(sm + L::W1H, FRS1 * 2, a.img + IMG_W1H, RS1 * 2);
+    if (SPLIT) {
+        copy_rows_to_lds<32>(sm + L::W2L, FRS2 * 2, a.img + IMG_W2L, RS2 * 2);
+        copy_rows_to_lds<4 * K1>(sm + L::W1L, FRS1 * 2, a.img + IMG_W1L, RS1 * 2);
+    }
+    copy_to_lds(sm + L::SMALL, a.img + IMG_B1, IMG_FWD_END - IMG_B1);
     __syncthreads();
-    const _Float16 *W2h = reinterpret_cast<const _Float16 *>(sm + F_W2H);
-    const _Float16 *W2l = reinterpret_cast<const _Float16 *>(sm + F_W2L);
-    const unsigned char *r1 = lds_region(sm, F_W1H);
-    const _Float16 *W1h = reinterpret_cast<const _Float16 *>(r1);
-    const _Float16 *W1l = reinterpret_cast<const _Float16 *>(r1 + (F_W1L - F_W1H));
-    const unsigned char *rs = r1 + (F_SMALL - F_W1H);
-    const float *b1 = reinterpret_cast<const float *>(rs);
-    const float *b2 = reinterpret_cast<const float *>(rs + (IMG_B2 - IMG_B1));
-    const float *W3 = reinterpret_cast<const float *>(rs + (IMG_W3 - IMG_B1));
+    const int ln = lane(), j = ln & 31, hf = ln >> 5;
+    const _Float16 *W2 = reinterpret_cast<const _Float16 *>(sm) + j * FRS2 + 8 * hf;
+    const unsigned char *r1 = lds_region(sm, L::W1H);
+    const _Float16 *W1 = reinterpret_cast<const _Float16 *>(r1) + j * FRS1 + 8 * hf;
+    constexpr int LO2 = (L::W2L - L::W2H) / 2, LO1 = (L::W1L - L::W1H) / 2;  // hi -> lo part, in halves
+    const unsigned char *rs = r1 + (L::SMALL - L::W1H);
+    const float *b1 = reinterpret_cast<const float *>(rs) + 4 * hf;
+    const float *b2 = reinterpret_cast<const float *>(rs + (IMG_B2 - IMG_B1)) + 4 * hf;
+    const float *W3 = reinterpret_cast<const float *>(rs + (IMG_W3 - IMG_B1)) + 4 * hf;
     const float *b3 = reinterpret_cast<const float *>(rs + (IMG_B3 - IMG_B1));
     const Meta meta = *reinterpret_cast<const Meta *>(rs + (IMG_META - IMG_B1));
-    const int ln = lane(), j = ln & 15, q = ln >> 4;
-    const int nwt = (a.S + FWD_WTILE - 1) / FWD_WTILE;
-    const int wt0 = blockIdx.x * FWD_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nwt = a.n_tiles;
+    // neighbouring tiles go to neighbouring blocks: a small batch spreads over the CUs
+    const int wt0 = blockIdx.x + (int)gridDim.x * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wstep = gridDim.x * FWD_WAVES;
     if (wt0 >= nwt) return;
-    // First ray of a wave tile's enclosing tile (past the last tile, the last tile's ray), read
-    // through the scalar cache: the index is wave-uniform and the table is read-only here.
+    // First ray of a tile (past the last tile, the last tile's ray), read through the scalar cache: the
+    // index is wave-uniform and the table is read-only here.
     const __attribute__((address_space(4))) int *tray = (const __attribute__((address_space(4))) int *)a.tile_ray;
-    auto first_ray = [&](int wt) { return tray[(wt < nwt ? wt : nwt - 1) / (TILE / FWD_WTILE)]; };
-    // sample points of a wave tile's feature lookups (the last sample's past the end)
-    auto points = [&](int wt, float (&p)[FWD_NC][3]) {
-#pragma unroll
-        for (int c = 0; c < FWD_NC; ++c) {
-            const int sp = min(wt * FWD_WTILE + 16 * c + j, a.S - 1);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) p[c][d] = a.xyz[3 * (int64_t)sp + d];
-        }
-    };
-    // The ray window entry and the sample points of the next tile are loaded one tile ahead,
-    // so their latency runs behind the products of the tile before.
-    // The output of a tile is stored at the head of the next one (after that tile's wait for its
-    // prefetched values), so that the wait does not include the store.
+    auto first_ray = [&](int wt) { return tray[wt < nwt ? wt : nwt - 1]; };
+    // The ray window entry and the sample points of the next tile are loaded one tile ahead, so their
+    // latency runs behind the products of the tile before.  The output of a tile is stored at the head of
+    // the next one (after that tile's wait for its prefetched values), so that the wait does not include
+    // the store.
     int r0 = first_ray(wt0);
     int win = window_entry(a.offs, a.n_rays, r0);
     int r0n = first_ray(wt0 + wstep);
-    float pt[FWD_NC][3];
-    if (GM) points(wt0, pt);
-    float zout[FWD_NC];
-    int sout[FWD_NC];
+    float pt[3] = {0.f, 0.f, 0.f};
+    auto points = [&](int wt) {  // the point of this lane's sample (the last sample's past the end)
+        const int sp = min(wt * TILE + j, a.S - 1);
 #pragma unroll
-    for (int c = 0; c < FWD_NC; ++c) sout[c] = -1;
-    auto store_out = [&]() {
-#pragma unroll
-        for (int c = 0; c < FWD_NC; ++c)
-            if (q < 3 && sout[c] >= 0) a.rgb[(int64_t)sout[c] * 3 + q] = zout[c];
+        for (int d = 0; d < 3; ++d) pt[d] = a.xyz[3 * (int64_t)sp + d];
     };
+    if (GM) points(wt0);
+    float zout = 0.f, zout2 = 0.f;
+    int sout = -1;
+    auto store_out = [&]() {  // colours 0 and 2 from the lower half of the wave, 1 from the upper
+        if (sout >= 0) {
+            a.rgb[(int64_t)sout * 3 + hf] = zout;
+            if (hf == 0) a.rgb[(int64_t)sout * 3 + 2] = zout2;
+        }
+    };
+    const float4 none = make_float4(0.f, 0.f, 0.f, 0.f);
+    const bool f0 = 4 * hf < a.in_feat, f1 = hf == 0 && 8 < a.in_feat;
     for (int wt = wt0; wt < nwt; wt += wstep) {
-        int s[FWD_NC], ex[FWD_NC], e1[FWD_NC];
-        bool sv[FWD_NC];
-        h8 xh[FWD_NC][2], xl[FWD_NC][2];
-        // this tile's inputs: every lane issues the same loads, with no divergent branch around them
-        // (divergent branches would make one lane group's loads wait for another's).  Slot group
-        // (kk, q): kk = 0 features 4q..4q+3 (view encoding 0..3 when q = 3) and view encoding
-        // 4+4q..7+4q; kk = 1 view encoding 20+4q..23+4q and padding.
-        float4 lo0[FWD_NC], hi0[FWD_NC], lo1[FWD_NC];
-        int ray[FWD_NC];
+        const int s = wt * TILE + j;
+        const bool sv = s < a.S;
+        const int sc = sv ? s : a.S - 1;
+        const int ray = min(ray_in_tile(a.offs, a.n_rays, r0, win, wt * TILE, s), a.n_rays - 1);
+        // This lane's inputs, slot groups (ks, i) = columns 16 ks + 8 i + 4 hf ..: features 4 hf .. and
+        // (hf = 0) 8 .. 11, view encoding 0..3 (hf = 1; FP16 mode), then encoding 4 + 4 hf, 12 + 4 hf,
+        // 20 + 4 hf, 28 + 4 hf (FP16 mode).  Split mode: the ray's bias row instead of the encoding.
+        float4 in[2 * K1], rb[SPLIT ? 16 : 1];
+        float rbmax = 0.f;
+        const float *pe = a.pe + (int64_t)ray * PEW + 4 * hf;
+        if (SPLIT) {
+            const float *row = a.rb + (int64_t)ray * RBW;
+            rbmax = row[H];
 #pragma unroll
-        for (int c = 0; c < FWD_NC; ++c) {
-            s[c] = wt * FWD_WTILE + 16 * c + j;
-            sv[c] = s[c] < a.S;
-            ray[c] = min(ray_in_window(a.offs, a.n_rays, r0, win, s[c]), a.n_rays - 1);
+            for (int i = 0; i < 16; ++i) rb[SPLIT ? i : 0] = *reinterpret_cast<const float4 *>(row + 8 * i + 4 * hf);
+        } else {
+#pragma unroll
+            for (int i = 2; i < 2 * K1; ++i) in[i] = *reinterpret_cast<const float4 *>(pe + 8 * i - 12);
         }
         store_out();  // the previous tile's output
-        // scalar load of a later tile's first ray, issued after the ray search so that the search's
-        // LDS waits do not wait for it (used one tile later)
-        const int r0f = first_ray(wt + 2 * wstep);
-#pragma unroll
-        for (int c = 0; c < FWD_NC; ++c) {
-            const int sc = sv[c] ? s[c] : a.S - 1;
-            const float *pe = a.pe + (int64_t)ray[c] * PEW;
-            const float4 v0 = *reinterpret_cast<const float4 *>(pe);
-            hi0[c] = *reinterpret_cast<const float4 *>(pe + 4 + 4 * q);
-            lo1[c] = *reinterpret_cast<const float4 *>(pe + 20 + 4 * q);
-            const bool fq = 4 * q < a.in_feat;  // never for q = 3 (at most 12 features)
-            float4 f;
-            if (GM) {
-                const Tri t = trilinear<GM == 2>(a.fg, pt[c][0], pt[c][1], pt[c][2]);
-                f = interp4(a.fg, t, fq ? 4 * q : 0);
-                if (a.feat_out && fq && sv[c])
-                    *reinterpret_cast<float4 *>(a.feat_out + (int64_t)s[c] * a.in_feat + 4 * q) = f;
-            } else if (a.feat_vec) {
-                f = *reinterpret_cast<const float4 *>(a.feat + (int64_t)sc * 12 + (fq ? 4 * q : 0));
-            } else {
-                f = fq ? feat4(a, sc, 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (GM) {
+            const Tri t = trilinear<GM == 2>(a.fg, pt[0], pt[1], pt[2]);
+            in[0] = interp4(a.fg, t, f0 ? 4 * hf : 0);
+            in[1] = none;
+            if (hf == 0) in[1] = interp4(a.fg, t, f1 ? 8 : 0);
+            if (a.feat_out && sv) {
+                float *fo = a.feat_out + (int64_t)s * a.in_feat;
+                if (f0) *reinterpret_cast<float4 *>(fo + 4 * hf) = in[0];
+                if (f1) *reinterpret_cast<float4 *>(fo + 8) = in[1];
             }
-            lo0[c] = q == 3 ? v0 : (fq ? f : make_float4(0.f, 0.f, 0.f, 0.f));
+            points(wt + wstep);
+        } else if (a.feat_vec) {
+            const float *fp = a.feat + (int64_t)sc * 12;
+            in[0] = *reinterpret_cast<const float4 *>(fp + 4 * hf);
+            in[1] = *reinterpret_cast<const float4 *>(fp + 8);
+        } else {
+            in[0] = f0 ? feat4(a, sc, 4 * hf) : none;
+            in[1] = f1 ? feat4(a, sc, 8) : none;
         }
-        // the next tile's ray window entry and sample points
+        if (!f0) in[0] = none;
+        if (!f1) in[1] = none;
+        if (!SPLIT && hf) in[1] = *reinterpret_cast<const float4 *>(pe - 4);
+        // the next tile's first ray and window entry (the scalar load of the one after goes ahead)
         r0 = r0n;
-        r0n = r0f;
+        r0n = first_ray(wt + 2 * wstep);
         win = window_entry(a.offs, a.n_rays, r0);
-        if (GM) points(wt + wstep, pt);
-#pragma unroll
-        for (int c = 0; c < FWD_NC; ++c) {
-            const bool v = sv[c];
-            const float xv[2][8] = {{v ? lo0[c].x : 0.f, v ? lo0[c].y : 0.f, v ? lo0[c].z : 0.f, v ? lo0[c].w : 0.f,
-                                     v ? hi0[c].x : 0.f, v ? hi0[c].y : 0.f, v ? hi0[c].z : 0.f, v ? hi0[c].w : 0.f},
-                                    {v ? lo1[c].x : 0.f, v ? lo1[c].y : 0.f, v ? lo1[c].z : 0.f, v ? lo1[c].w : 0.f,
-                                     0.f, 0.f, 0.f, 0.f}};
+        h8 xh[K1], xl[K1];
+        float un1, sc1, un2;
+        {
             float m = 0.f;
 #pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
+            for (int g = 0; g < 2 * K1; ++g) {
+                if (!sv) in[g] = none;
+                m = fmaxf(m, fmaxf(fmaxf(fabsf(in[g].x), fabsf(in[g].y)), fmaxf(fabsf(in[g].z), fabsf(in[g].w))));
+            }
+            m = fmaxf(m, other_half(m));
+            const int ex = scale_exp(m), e1 = scale_exp(SPLIT ? meta.n1f * m + rbmax : meta.n1 * m + meta.b1max);
+            const float sx = pow2(ex);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(xv[kk][e]));
-            m = fmaxf(m, __shfl_xor(m, 16, 64));
-            m = fmaxf(m, __shfl_xor(m, 32, 64));
-            ex[c] = scale_exp(m);
-            e1[c] = scale_exp(meta.n1 * m + meta.b1max);
-            const float sc = pow2(ex[c]);
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
+            for (int ks = 0; ks < K1; ++ks) {
                 h4 h0, l0, h1, l1;
-                split4<true>(&xv[kk][0], sc, h0, l0);
-                split4<true>(&xv[kk][4], sc, h1, l1);
-                xh[c][kk] = cat(h0, h1);
-                xl[c][kk] = cat(l0, l1);
+                const float v0[4] = {in[2 * ks].x, in[2 * ks].y, in[2 * ks].z, in[2 * ks].w};
+                const float v1[4] = {in[2 * ks + 1].x, in[2 * ks + 1].y, in[2 * ks + 1].z, in[2 * ks + 1].w};
+                split4<true>(v0, sx, h0, l0);
+                split4<true>(v1, sx, h1, l1);
+                xh[ks] = cat(h0, h1);
+                xl[ks] = cat(l0, l1);
             }
+            un1 = pow2(-(meta.sw1 + ex));
+            sc1 = pow2(e1);
+            un2 = pow2(-(meta.sw2 + e1));
         }
-        // layer 1: h1 = relu(W1 x + b1), kept as the split B operand of layer 2
-        h4 hh[FWD_NC][8], hl[FWD_NC][8];
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            v4f acc[FWD_NC];
-#pragma unroll
-            for (int c = 0; c < FWD_NC; ++c) acc[c] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk) {
-                const int o = (16 * m + j) * FRS1 + 32 * kk + 8 * q;
-                const h8 ah = *reinterpret_cast<const h8 *>(W1h + o);
-                const h8 al = *reinterpret_cast<const h8 *>(W1l + o);
-                if (SPLIT) {
-#pragma unroll
-                    for (int c = 0; c < FWD_NC; ++c) acc[c] = mfma16(al, xh[c][kk], acc[c]);
-#pragma unroll
-                    for (int c = 0; c < FWD_NC; ++c) acc[c] = mfma16(ah, xl[c][kk], acc[c]);
-                }
-#pragma unroll
-                for (int c = 0; c < FWD_NC; ++c) acc[c] = mfma16(ah, xh[c][kk], acc[c]);
+        // Eight stages, one row tile each: 0..3 layer 1 (K1 K-steps), 4..7 layer 2 (8).  The products of a
+        // stage run with the vector work that ends the stage before it (bias, ReLU, split; or bias, ReLU
+        // and the output layer), in four pieces of four units, so that a wave keeps both units busy.  The
+        // weight operands of the K-steps come from LDS one step ahead (two register sets).  Each K-step is fenced for the scheduler, which otherwise puts every read right before its
+        // products and the vector work after them.
+        constexpr int G1 = 4 * K1, G = G1 + 32;
+        h8 wh[2], wl[2];
+        auto fetch = [&](int g) {
+            const int m = g < G1 ? g / K1 : (g - G1) / 8, ks = g < G1 ? g % K1 : (g - G1) % 8;
+            const _Float16 *w = g < G1 ? W1 + 32 * m * FRS1 + 16 * ks : W2 + 32 * m * FRS2 + 16 * ks;
+            wh[g % 2] = *reinterpret_cast<const h8 *>(w);
+            if (SPLIT) wl[g % 2] = *reinterpret_cast<const h8 *>(w + (g < G1 ? LO1 : LO2));
+        };
+        v16f acc[2];
+        auto products = [&](int g, h8 bh, h8 bl, v16f &c) {
+            if (g + 1 < G) fetch(g + 1);
+            if (SPLIT) {
+                c = mfma32(wl[g % 2], bh, c);
+                c = mfma32(wh[g % 2], bl, c);
             }
-            const float4 bb = *reinterpret_cast<const float4 *>(b1 + 16 * m + 4 * q);
-#pragma unroll
-            for (int c = 0; c < FWD_NC; ++c) {
-                const float un = pow2(-(meta.sw1 + ex[c]));
-                float v[4] = {fmaxf(fmaf(acc[c][0], un, bb.x), 0.f), fmaxf(fmaf(acc[c][1], un, bb.y), 0.f),
-                              fmaxf(fmaf(acc[c][2], un, bb.z), 0.f), fmaxf(fmaf(acc[c][3], un, bb.w), 0.f)};
-                split4<true>(v, pow2(e1[c]), hh[c][m], hl[c][m]);
-            }
-            // keep the scheduler from hoisting every weight load of the layer (spills)
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // layer 2 and the output layer: z3 = W3 relu(W2 h1 + b2) (+ b3), output rows on VALU
-        float z[FWD_NC][3];
-#pragma unroll
-        for (int c = 0; c < FWD_NC; ++c) z[c][0] = z[c][1] = z[c][2] = 0.f;
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            v4f acc[FWD_NC];
-#pragma unroll
-            for (int c = 0; c < FWD_NC; ++c) acc[c] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const int o = (16 * m + j) * FRS2 + 32 * kk + 8 * q;
-                const h8 ah = *reinterpret_cast<const h8 *>(W2h + o);
-                const h8 al = *reinterpret_cast<const h8 *>(W2l + o);
-                if (SPLIT) {
-#pragma unroll
-                    for (int c = 0; c < FWD_NC; ++c) {
-                        const h8 bh = cat(hh[c][2 * kk], hh[c][2 * kk + 1]);
-                        acc[c] = mfma16(al, bh, acc[c]);
-                    }
-#pragma unroll
-                    for (int c = 0; c < FWD_NC; ++c)
-                        acc[c] = mfma16(ah, cat(hl[c][2 * kk], hl[c][2 * kk + 1]), acc[c]);
-                }
-#pragma unroll
-                for (int c = 0; c < FWD_NC; ++c) acc[c] = mfma16(ah, cat(hh[c][2 * kk], hh[c][2 * kk + 1]), acc[c]);
-            }
-            const float4 bb = *reinterpret_cast<const float4 *>(b2 + 16 * m + 4 * q);
-            const float4 w0 = *reinterpret_cast<const float4 *>(W3 + 16 * m + 4 * q);
-            const float4 w1 = *reinterpret_cast<const float4 *>(W3 + H + 16 * m + 4 * q);
-            const float4 w2 = *reinterpret_cast<const float4 *>(W3 + 2 * H + 16 * m + 4 * q);
+            c = mfma32(wh[g % 2], bh, c);
+        };
+        // piece i of the end of layer 1's row tile m: half i % 2 of h1's K-step 2 m + i / 2
+        h4 hh[16], hl[16];
+        auto end1 = [&](int m, int i, const v16f &c) {
+            const float4 bb = SPLIT ? rb[SPLIT ? 4 * m + i : 0] : *reinterpret_cast<const float4 *>(b1 + 32 * m + 8 * i);
+            const int r = 4 * i;
+            const float v[4] = {fmaxf(fmaf(c[r], un1, bb.x), 0.f), fmaxf(fmaf(c[r + 1], un1, bb.y), 0.f),
+                                fmaxf(fmaf(c[r + 2], un1, bb.z), 0.f), fmaxf(fmaf(c[r + 3], un1, bb.w), 0.f)};
+            split4<true>(v, sc1, hh[4 * m + i], hl[4 * m + i]);
+        };
+        // piece i of the end of layer 2's row tile m: z3 += W3 relu(W2 h1 + b2), output rows on VALU
+        float z[3] = {0.f, 0.f, 0.f};
+        auto end2 = [&](int m, int i, const v16f &c) {
+            const int u = 32 * m + 8 * i;
+            const float4 bb = *reinterpret_cast<const float4 *>(b2 + u);
+            const float4 w0 = *reinterpret_cast<const float4 *>(W3 + u);
+            const float4 w1 = *reinterpret_cast<const float4 *>(W3 + H + u);
+            const float4 w2 = *reinterpret_cast<const float4 *>(W3 + 2 * H + u);
             const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
             const float wv[3][4] = {{w0.x, w0.y, w0.z, w0.w}, {w1.x, w1.y, w1.z, w1.w}, {w2.x, w2.y, w2.z, w2.w}};
 #pragma unroll
-            for (int c = 0; c < FWD_NC; ++c) {
-                const float un = pow2(-(meta.sw2 + e1[c]));
+            for (int r = 0; r < 4; ++r) {
+                const float h2 = fmaxf(fmaf(c[4 * i + r], un2, bv[r]), 0.f);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float h2 = fmaxf(fmaf(acc[c][r], un, bv[r]), 0.f);
+                for (int o = 0; o < 3; ++o) z[o] += wv[o][r] * h2;
+            }
+        };
+        fetch(0);
 #pragma unroll
-                    for (int o = 0; o < 3; ++o) z[c][o] += wv[o][r] * h2;
+        for (int m = 0; m < 4; ++m) {
+            v16f &c = acc[m & 1];
+            const v16f &prev = acc[(m & 1) ^ 1];
+            c = v16f{};
+#pragma unroll
+            for (int ks = 0; ks < K1; ++ks) {
+                products(K1 * m + ks, xh[ks], xl[ks], c);
+                if (m > 0) {
+#pragma unroll
+                    for (int i = ks * 4 / K1; i < (ks + 1) * 4 / K1; ++i) end1(m - 1, i, prev);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int c = 0; c < FWD_NC; ++c) {
+        for (int m = 0; m < 4; ++m) {
+            v16f &c = acc[m & 1];
+            const v16f &prev = acc[(m & 1) ^ 1];
+            c = v16f{};
 #pragma unroll
-            for (int o = 0; o < 3; ++o) {
-                z[c][o] += __shfl_xor(z[c][o], 16, 64);
-                z[c][o] += __shfl_xor(z[c][o], 32, 64);
+            for (int ks = 0; ks < 8; ++ks) {
+                products(G1 + 8 * m + ks, cat(hh[2 * ks], hh[2 * ks + 1]), cat(hl[2 * ks], hl[2 * ks + 1]), c);
+                if (m == 0 && ks < 4) end1(3, ks, prev);
+                if (m > 0 && (ks & 1)) end2(m - 1, ks >> 1, prev);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            const float zq = q == 0 ? z[c][0] : (q == 1 ? z[c][1] : z[c][2]);
-            zout[c] = fast_sigmoid(zq + b3[q < 3 ? q : 0]);
-            sout[c] = sv[c] ? s[c] : -1;
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) end2(3, i, acc[1]);
+#pragma unroll
+        for (int o = 0; o < 3; ++o) z[o] += other_half(z[o]);
+        zout = fast_sigmoid((hf ? z[1] : z[0]) + b3[hf]);
+        zout2 = fast_sigmoid(z[2] + b3[2]);
+        sout = sv ? s : -1;
     }
     store_out();
 }
@@ -1608,10 +1674,13 @@ int bwd_blocks(int64_t S) {
     return (int)(t < MAX_BLOCKS ? (t < 1 ? 1 : t) : MAX_BLOCKS);
 }
 
-size_t ws_layout(const dvgo_color_mlp *m, int32_t R, int64_t S, size_t *off_pe, size_t *off_tr, size_t *off_part) {
+size_t ws_layout(const dvgo_color_mlp *m, int32_t R, int64_t S, size_t *off_pe, size_t *off_rb, size_t *off_tr,
+                 size_t *off_part) {
     size_t o = align_up((size_t)IMG_BYTES, 256);
     *off_pe = o;
     o += align_up((size_t)R * PEW * 4, 256);
+    *off_rb = o;
+    o += align_up((size_t)R * RBW * 4, 256);
     *off_tr = o;
     o += align_up((size_t)((S + TILE - 1) / TILE) * 4, 256);
     *off_part = o;
@@ -1627,8 +1696,8 @@ int setup(const dvgo_color_mlp *m, int32_t R, const int32_t *offs, const float *
     if (S >= ((int64_t)1 << 31) / 16) return set_error(DVGO_ERR_RANGE, "n_samples too large");
     if (S > 0 && (R == 0 || !offs || !dirs || (need_feat && !feat)))
         return set_error(DVGO_ERR_NULL, "ray_offsets, dirs or feat is NULL");
-    size_t off_pe, off_tr, off_part;
-    const size_t need = ws_layout(m, R, S, &off_pe, &off_tr, &off_part);
+    size_t off_pe, off_rb, off_tr, off_part;
+    const size_t need = ws_layout(m, R, S, &off_pe, &off_rb, &off_tr, &off_part);
     if (!ws || ws_bytes < need) return set_error(DVGO_ERR_WORKSPACE, "workspace too small (%zu < %zu)", ws_bytes, need);
     if (((uintptr_t)ws & 255) != 0) return set_error(DVGO_ERR_SHAPE, "workspace must be 256-byte aligned");
     memset(&a, 0, sizeof(a));
@@ -1646,6 +1715,7 @@ int setup(const dvgo_color_mlp *m, int32_t R, const int32_t *offs, const float *
     a.feat_vec = m->in_feat == 12 && ((uintptr_t)feat & 15) == 0;
     a.img = (unsigned char *)ws;
     a.pe = (float *)((char *)ws + off_pe);
+    a.rb = (float *)((char *)ws + off_rb);
     a.tile_ray = (int *)((char *)ws + off_tr);
     a.n_tiles = (int)((S + TILE - 1) / TILE);
     a.partial = (float *)((char *)ws + off_part);
@@ -1655,19 +1725,16 @@ int setup(const dvgo_color_mlp *m, int32_t R, const int32_t *offs, const float *
 
 template <int GM>
 int launch_fwd(const MlpArgs &a, const dvgo_color_mlp *m, hipStream_t st) {
-    using F = FwdShape<GM>;
-    const int64_t nwt = (a.S + F::WTILE - 1) / F::WTILE;
-    const int64_t nb = (nwt + F::WAVES - 1) / F::WAVES;
-    const dim3 grid((int)(nb < MAX_BLOCKS ? nb : MAX_BLOCKS));
+    const dim3 grid(a.n_tiles < MAX_BLOCKS ? a.n_tiles : MAX_BLOCKS);
     if (m->precision == DVGO_MLP_F16)
-        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM>), grid, dim3(F::THREADS), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM>), grid, dim3(FWD_THREADS), 0, st, a);
     else
-        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM>), grid, dim3(F::THREADS), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM>), grid, dim3(FWD_THREADS), 0, st, a);
     return check_hip(hipGetLastError(), "mlp_fwd_kernel launch");
 }
 
 int launch_prep(const MlpArgs &a, hipStream_t st) {
-    const int n = PREP_FIXED_BLOCKS + (a.n_rays + PREP_THREADS - 1) / PREP_THREADS +
+    const int n = PREP_FIXED_BLOCKS + (a.n_rays + PREP_RAYS - 1) / PREP_RAYS +
                   (a.n_tiles + PREP_THREADS - 1) / PREP_THREADS;
     hipLaunchKernelGGL(mlp_prep_kernel, dim3(n), dim3(PREP_THREADS), 0, st, a);
     return check_hip(hipGetLastError(), "mlp_prep_kernel launch");
@@ -1680,8 +1747,8 @@ extern "C" int dvgo_mlp_workspace_size(const dvgo_color_mlp *m, int32_t n_rays, 
     if (rc) return rc;
     if (!bytes) return set_error(DVGO_ERR_NULL, "bytes is NULL");
     if (n_rays < 0 || n_samples < 0) return set_error(DVGO_ERR_SHAPE, "negative size");
-    size_t a, b, c;
-    *bytes = ws_layout(m, n_rays, n_samples, &a, &b, &c);
+    size_t a, b, c, d;
+    *bytes = ws_layout(m, n_rays, n_samples, &a, &b, &c, &d);
     return DVGO_OK;
 }
 
@@ -1794,8 +1861,8 @@ extern "C" int dvgo_mlp_reduce_grads(const dvgo_color_mlp *m, int32_t n_rays, in
     if (rc) return rc;
     if (n_rays < 0 || n_samples < 0) return set_error(DVGO_ERR_SHAPE, "negative n_rays or n_samples");
     if (n_samples >= ((int64_t)1 << 31) / 16) return set_error(DVGO_ERR_RANGE, "n_samples too large");
-    size_t off_pe, off_tr, off_part;
-    const size_t need = ws_layout(m, n_rays, n_samples, &off_pe, &off_tr, &off_part);
+    size_t off_pe, off_rb, off_tr, off_part;
+    const size_t need = ws_layout(m, n_rays, n_samples, &off_pe, &off_rb, &off_tr, &off_part);
     if (!ws || ws_bytes < need) return set_error(DVGO_ERR_WORKSPACE, "workspace too small (%zu < %zu)", ws_bytes, need);
     if (((uintptr_t)ws & 255) != 0) return set_error(DVGO_ERR_SHAPE, "workspace must be 256-byte aligned");
     if (n_samples == 0) return DVGO_OK;
