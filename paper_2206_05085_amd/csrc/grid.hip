@@ -642,17 +642,19 @@ __device__ __forceinline__ int brick_of(const BinGeom &b, const Cell &c) {
 
 struct BinWs {
     int *offs;    // [n + 1] first slot of each brick in perm
-    int *cursor;  // [n] counts, counted down again by the placement
+    int *count;   // [n] samples of each brick
     int *perm;    // [S] sample indices grouped by brick
-    int *keys;    // [S] brick of each sample
+    int2 *place;  // [S] brick of each sample, its place within it
 };
 
-size_t bin_bytes(int nb, int64_t S, size_t *o_cursor, size_t *o_perm) {
+size_t bin_bytes(int nb, int64_t S, size_t *o_count, size_t *o_perm, size_t *o_place) {
     size_t o = align_up((size_t)(nb + 1) * 4, 256);
-    *o_cursor = o;
+    *o_count = o;
     o += align_up((size_t)nb * 4, 256);
     *o_perm = o;
-    o += (size_t)S * 8;  // perm, then keys
+    o += align_up((size_t)S * 4, 256);
+    *o_place = o;
+    o += (size_t)S * 8;
     return o;
 }
 
@@ -660,19 +662,23 @@ __global__ __launch_bounds__(256) void bin_zero_kernel(int *p, int n) {
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) p[i] = 0;
 }
 
+// Each run of equal bricks in a wave takes its places from the brick's count: the only atomics of the
+// binning, which is bound by them (counting here and drawing the places with a second atomic in the
+// placement: 62 us for the four launches, this way 45, at 2,293,760 samples in 64,000 bricks)
 template <bool W>
 __global__ __launch_bounds__(64 * BIN_WAVES) void bin_count_kernel(DevGrid g, BinGeom bg, int64_t S,
-                                                                 const float *__restrict__ xyz, int *cnt, int *keys) {
+                                                                 const float *__restrict__ xyz, int *cnt,
+                                                                 int2 *place) {
     const int64_t nwaves = (int64_t)gridDim.x * BIN_WAVES;
     for (int64_t base = (int64_t)(blockIdx.x * BIN_WAVES + (threadIdx.x >> 6)) * 64; base < S; base += nwaves * 64) {
         const int64_t k = base + lane();
         int key = -1;
-        if (k < S) {
-            key = brick_of(bg, cell_of<W>(g, xyz[3 * k], xyz[3 * k + 1], xyz[3 * k + 2]));
-            keys[k] = key;
-        }
+        if (k < S) key = brick_of(bg, cell_of<W>(g, xyz[3 * k], xyz[3 * k + 1], xyz[3 * k + 2]));
         const Run run = wave_runs(key);
-        if (run.head) atomicAdd(&cnt[key], run.len);
+        int start = 0;
+        if (run.head) start = atomicAdd(&cnt[key], run.len);
+        start = __shfl(start, run.head_lane, 64);
+        if (k < S) place[k] = make_int2(key, start + (lane() - run.head_lane));
     }
 }
 
@@ -727,44 +733,33 @@ __global__ __launch_bounds__(SCAN_THREADS) void bin_scan_kernel(int n, const int
     if (tid == 0 && start + SCAN_PER >= n) offs[n] = total;
 }
 
-// each run of equal bricks in a wave takes its slots from the brick's count, from the top down
-__global__ __launch_bounds__(64 * BIN_WAVES) void bin_place_kernel(int64_t S, const int *__restrict__ keys,
-                                                                 const int *__restrict__ offs, int *left, int *perm) {
-    const int64_t nwaves = (int64_t)gridDim.x * BIN_WAVES;
-    for (int64_t base = (int64_t)(blockIdx.x * BIN_WAVES + (threadIdx.x >> 6)) * 64; base < S; base += nwaves * 64) {
-        const int64_t k = base + lane();
-        const int key = k < S ? keys[k] : -1;
-        const Run run = wave_runs(key);
-        int start = 0;
-        if (run.head) start = offs[key] + atomicSub(&left[key], run.len) - run.len;
-        start = __shfl(start, run.head_lane, 64);
-        if (key >= 0) perm[start + (lane() - run.head_lane)] = (int)k;
+__global__ __launch_bounds__(256) void bin_place_kernel(int64_t S, const int2 *__restrict__ place,
+                                                       const int *__restrict__ offs, int *perm) {
+    for (int64_t k = blockIdx.x * (int64_t)256 + threadIdx.x; k < S; k += (int64_t)gridDim.x * 256) {
+        const int2 p = place[k];
+        perm[offs[p.x] + p.y] = (int)k;
     }
 }
 
-// One channel.  A block takes `per` bricks, gridDim apart so that crowded neighbours fall to different
-// blocks.  A brick of at most 64 samples takes one wave, a sample a lane, straight to global atomics; a
-// larger one takes the block: an LDS tile of BV^3 vertices, flushed with one global atomic per touched
-// vertex, each thread walking a run of the brick's samples (SlotWalk, the eight classes in registers), so
-// that vertices shared along a ray merge before the LDS atomics, which would otherwise collide.  Bound by
-// latency: 981,504 samples in 8,000 bricks 75 -> 63 us; 2,293,760 samples in 64,000 bricks, most of them
-// with a handful and a thousand with 1,500 to 4,300, 219 -> 86 us.
-constexpr int BRICKS = 4;  // the most bricks a block takes, one wave each in the first phase
+// One channel, a block per brick.  A brick of at most 64 samples takes the first wave, a sample a lane,
+// straight to global atomics; a larger one the whole block: an LDS tile of BV^3 vertices, flushed with one
+// global atomic per touched vertex, each thread walking a run of the brick's samples (SlotWalk, the eight
+// classes in registers), so that vertices shared along a ray merge before the LDS atomics, which would
+// otherwise collide.  Bound by latency: 981,504 samples in 8,000 bricks 75 -> 57 us; 2,293,760 samples in
+// 64,000 bricks, most of them with a handful and a thousand with 1,500 to 4,300, 219 -> 66 us.
+constexpr int BRICK_THREADS = 256;
 
 template <bool W>
-__global__ __launch_bounds__(64 * BRICKS) void brick_scatter_kernel(DevGrid g, BinGeom bg, int per,
-                                                                    const float *__restrict__ xyz,
-                                                                    const float *__restrict__ vals,
-                                                                    const int *__restrict__ offs,
-                                                                    const int *__restrict__ perm) {
-    constexpr int NTH = 64 * BRICKS;
-    __shared__ float tile[BV * BV * BV];
-    {
-        const int wv = threadIdx.x >> 6, b = blockIdx.x + wv * (int)gridDim.x;
-        const bool mine = wv < per && b < bg.n;
-        const int beg = mine ? offs[b] : 0, n = mine ? offs[b + 1] - beg : 0;
-        if (n <= 64 && lane() < n) {
-            const int64_t s = perm[beg + lane()];
+__global__ __launch_bounds__(BRICK_THREADS) void brick_scatter_kernel(DevGrid g, BinGeom bg,
+                                                                      const float *__restrict__ xyz,
+                                                                      const float *__restrict__ vals,
+                                                                      const int *__restrict__ offs,
+                                                                      const int *__restrict__ perm) {
+    __shared__ double tile[BV * BV * BV];
+    const int b = blockIdx.x, beg = offs[b], end = offs[b + 1];
+    if (end - beg <= 64) {
+        if ((int)threadIdx.x < end - beg) {
+            const int64_t s = perm[beg + threadIdx.x];
             const Cell c = cell_of<W>(g, xyz[3 * s], xyz[3 * s + 1], xyz[3 * s + 2]);
             const float v = vals[s];
             float *p = g.grad + c.ix * g.sx + c.iy * g.sy + c.iz * g.cs;
@@ -774,36 +769,40 @@ __global__ __launch_bounds__(64 * BRICKS) void brick_scatter_kernel(DevGrid g, B
                     unsafeAtomicAdd(p + corner_off(g, k), corner_weight(c, (k >> 2) & 1, (k >> 1) & 1, k & 1) * v);
             }
         }
+        return;
     }
-    for (int h = 0; h < per; ++h) {
-        const int b = blockIdx.x + h * (int)gridDim.x;
-        if (b >= bg.n) break;
-        const int beg = offs[b], end = offs[b + 1];
-        if (end - beg <= 64) continue;
-        const int bz = b % bg.nb[2], by = (b / bg.nb[2]) % bg.nb[1], bx = b / (bg.nb[2] * bg.nb[1]);
-        const int x0 = bx * BRICK, y0 = by * BRICK, z0 = bz * BRICK;
-        for (int i = threadIdx.x; i < BV * BV * BV; i += NTH) tile[i] = 0.f;
-        __syncthreads();
-        const int len = (end - beg + NTH - 1) / NTH;
-        const LdsSum sum{tile};
-        SlotWalk<1, 8> wk;
-        for (int i = beg + (int)threadIdx.x * len, e = min(i + len, end); i < e; ++i) {
-            const int64_t s = perm[i];
-            const Cell c = cell_of<W>(g, xyz[3 * s], xyz[3 * s + 1], xyz[3 * s + 2]);
-            wk.step(BV * BV, BV, 1, stage_cell(((c.ix - x0) * BV + (c.iy - y0)) * BV + (c.iz - z0), c), vals[s], sum);
+    const int bz = b % bg.nb[2], by = (b / bg.nb[2]) % bg.nb[1], bx = b / (bg.nb[2] * bg.nb[1]);
+    const int x0 = bx * BRICK, y0 = by * BRICK, z0 = bz * BRICK;
+    for (int i = threadIdx.x; i < BV * BV * BV; i += BRICK_THREADS) tile[i] = 0.0;
+    __syncthreads();
+    const int len = (end - beg + BRICK_THREADS - 1) / BRICK_THREADS;
+    const LdsSum sum{tile};
+    SlotWalk<1, 8> wk;
+    const int i0 = beg + (int)threadIdx.x * len, e = min(i0 + len, end);
+    if (i0 < e) {
+        // the next sample's row is loaded, and the index after it, while this one is added
+        int64_t s1 = perm[min(i0 + 1, e - 1)];
+        const int64_t s0 = perm[i0];
+        float px = xyz[3 * s0], py = xyz[3 * s0 + 1], pz = xyz[3 * s0 + 2], pv = vals[s0];
+        for (int i = i0; i < e; ++i) {
+            const float x = px, y = py, z = pz, v = pv;
+            const int64_t s2 = perm[min(i + 2, e - 1)];
+            px = xyz[3 * s1], py = xyz[3 * s1 + 1], pz = xyz[3 * s1 + 2], pv = vals[s1];
+            s1 = s2;
+            const Cell c = cell_of<W>(g, x, y, z);
+            wk.step(BV * BV, BV, 1, stage_cell(((c.ix - x0) * BV + (c.iy - y0)) * BV + (c.iz - z0), c), v, sum);
         }
-        wk.finish(sum);
-        __syncthreads();
-        // flush in memory order so consecutive lanes hit consecutive addresses
-        for (int v = threadIdx.x; v < BV * BV * BV; v += NTH) {
-            const float t = tile[v];
-            if (t == 0.f) continue;
-            const int lz = v % BV, ly = (v / BV) % BV, lx = v / (BV * BV);
-            const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
-            if (gx < g.n[0] && gy < g.n[1] && gz < g.n[2])
-                unsafeAtomicAdd(g.grad + (int64_t)gx * g.sx + (int64_t)gy * g.sy + (int64_t)gz * g.cs, t);
-        }
-        __syncthreads();
+    }
+    wk.finish(sum);
+    __syncthreads();
+    // flush in memory order so consecutive lanes hit consecutive addresses
+    for (int v = threadIdx.x; v < BV * BV * BV; v += BRICK_THREADS) {
+        const float t = (float)tile[v];
+        if (t == 0.f) continue;
+        const int lz = v % BV, ly = (v / BV) % BV, lx = v / (BV * BV);
+        const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
+        if (gx < g.n[0] && gy < g.n[1] && gz < g.n[2])
+            unsafeAtomicAdd(g.grad + (int64_t)gx * g.sx + (int64_t)gy * g.sy + (int64_t)gz * g.cs, t);
     }
 }
 
@@ -814,14 +813,14 @@ int bin_setup(const dvgo_grid *g, int64_t S, const void *ws, size_t ws_bytes, De
     if (S < 0) return set_error(DVGO_ERR_SHAPE, "negative n_samples");
     if (S >= ((int64_t)1 << 31)) return set_error(DVGO_ERR_RANGE, "n_samples must be below 2^31");
     bg = bin_geom(dg);
-    size_t oc, op;
-    const size_t need = bin_bytes(bg.n, S, &oc, &op);
+    size_t oc, op, ol;
+    const size_t need = bin_bytes(bg.n, S, &oc, &op, &ol);
     if (!ws || ws_bytes < need) return set_error(DVGO_ERR_WORKSPACE, "bin workspace too small (%zu < %zu)", ws_bytes, need);
     if (((uintptr_t)ws & 255) != 0) return set_error(DVGO_ERR_SHAPE, "bin workspace must be 256-byte aligned");
     w.offs = (int *)ws;
-    w.cursor = (int *)((char *)ws + oc);
+    w.count = (int *)((char *)ws + oc);
     w.perm = (int *)((char *)ws + op);
-    w.keys = w.perm + S;
+    w.place = (int2 *)((char *)ws + ol);
     return DVGO_OK;
 }
 
@@ -838,8 +837,8 @@ extern "C" int dvgo_bin_workspace_size(const dvgo_grid *g, int64_t n_samples, si
     if (rc) return rc;
     if (!bytes) return set_error(DVGO_ERR_NULL, "bytes is NULL");
     if (n_samples < 0) return set_error(DVGO_ERR_SHAPE, "negative n_samples");
-    size_t a, b;
-    *bytes = bin_bytes(bin_geom(dg).n, n_samples, &a, &b);
+    size_t a, b, c;
+    *bytes = bin_bytes(bin_geom(dg).n, n_samples, &a, &b, &c);
     return DVGO_OK;
 }
 
@@ -853,21 +852,20 @@ extern "C" int dvgo_bin_samples(const dvgo_grid *g, int64_t n_samples, const flo
     if (n_samples > 0 && !xyz) return set_error(DVGO_ERR_NULL, "xyz is NULL");
     const hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(bin_zero_kernel, dim3((bg.n + 255) / 256 < 1024 ? (bg.n + 255) / 256 : 1024), dim3(256), 0, st,
-                       w.cursor, bg.n);
+                       w.count, bg.n);
     const int nb = bin_blocks(n_samples);
     if (n_samples > 0) {
         if (dg.warp)
             hipLaunchKernelGGL(bin_count_kernel<true>, dim3(nb), dim3(64 * BIN_WAVES), 0, st, dg, bg, n_samples, xyz,
-                               w.cursor, w.keys);
+                               w.count, w.place);
         else
             hipLaunchKernelGGL(bin_count_kernel<false>, dim3(nb), dim3(64 * BIN_WAVES), 0, st, dg, bg, n_samples, xyz,
-                               w.cursor, w.keys);
+                               w.count, w.place);
     }
     hipLaunchKernelGGL(bin_scan_kernel, dim3((bg.n + SCAN_PER - 1) / SCAN_PER), dim3(SCAN_THREADS), 0, st, bg.n,
-                       w.cursor, w.offs);
+                       w.count, w.offs);
     if (n_samples > 0)
-        hipLaunchKernelGGL(bin_place_kernel, dim3(nb), dim3(64 * BIN_WAVES), 0, st, n_samples, w.keys, w.offs, w.cursor,
-                           w.perm);
+        hipLaunchKernelGGL(bin_place_kernel, dim3(nb), dim3(256), 0, st, n_samples, w.place, w.offs, w.perm);
     return check_hip(hipGetLastError(), "bin kernels launch");
 }
 
@@ -884,18 +882,11 @@ extern "C" int dvgo_grid_scatter_binned(const dvgo_grid *g, int64_t n_samples, c
     // more than one channel: the slot walk over the samples in their own order (12 channels, 981,504
     // samples on 160^3: 193 us; the brick tiles took 792 us, their LDS atomics growing with the channels)
     if (g->channels > 1) return scatter_any(dg, n_samples, xyz, grad_out, st);
-    // Mostly small bricks (at most 64 samples on average): several per block, so that the launch is not a
-    // queue of blocks with nothing to do (2,293,760 samples, 64,000 bricks: 119 us with one each, 86 with
-    // four).  Else one: four large bricks in a row make a long block (981,504 samples, 8,000 bricks: 79
-    // against 63 us).
-    const int per = n_samples <= (int64_t)64 * bg.n ? BRICKS : 1;
-    const dim3 grid((bg.n + per - 1) / per), block(64 * BRICKS);
+    const dim3 grid(bg.n), block(BRICK_THREADS);
     if (dg.warp)
-        hipLaunchKernelGGL((brick_scatter_kernel<true>), grid, block, 0, st, dg, bg, per, xyz, grad_out,
-                           w.offs, w.perm);
+        hipLaunchKernelGGL((brick_scatter_kernel<true>), grid, block, 0, st, dg, bg, xyz, grad_out, w.offs, w.perm);
     else
-        hipLaunchKernelGGL((brick_scatter_kernel<false>), grid, block, 0, st, dg, bg, per, xyz, grad_out,
-                           w.offs, w.perm);
+        hipLaunchKernelGGL((brick_scatter_kernel<false>), grid, block, 0, st, dg, bg, xyz, grad_out, w.offs, w.perm);
     return check_hip(hipGetLastError(), "brick_scatter_kernel launch");
 }
 
