@@ -3,7 +3,7 @@
 //
 // Split precision.  Every matrix operand v is held as two FP16 parts scaled by a power of
 // two, v 2^e = hi + lo with hi = fp16(v 2^e) and lo = fp16(v 2^e - hi), and a product is
-// taken as hi*hi' + hi*lo' + lo*hi' (three v_mfma_f32_16x16x32_f16 into one FP32
+// taken as hi*hi' + hi*lo' + lo*hi' (three FP16 matrix instructions into one FP32
 // accumulator).  The dropped lo*lo' term and the rounding of lo leave a relative error near
 // 2^-22 per product.  The power of two keeps operands inside the FP16 normal range: weight
 // matrices use one exponent each (largest entry just under 2^14); an activation column (one
@@ -11,22 +11,20 @@
 // its own (infinity norms of the weights times the sample's input or upstream gradient).
 // Accumulators are brought back to true scale with v_ldexp, which is exact.
 //
-// Layout.  A 16x16 accumulator tile holds 16 hidden units (rows) x 16 samples (columns);
-// lane (q = lane/16, j = lane%16) owns rows 4q..4q+3 of column j.  A K-step of 32 reads
-// the lane's 8 operand slots (q, e) as logical index k(kk, q, e) = 32 kk + 4 q + e (e < 4)
-// or 32 kk + 16 + 4 q + (e - 4) (e >= 4), so two consecutive row tiles of one layer's
-// output are the next layer's B operand without any data movement.  Weight rows are
-// stored with their columns in that slot order ("phys" order), so an A operand is one
+// Layout.  The forward works on 32x32 accumulator tiles (see its section).  In the backward a 16x16
+// accumulator tile holds 16 hidden units (rows) x 16 samples (columns); lane (q = lane/16, j = lane%16)
+// owns rows 4q..4q+3 of column j.  A K-step of 32 reads the lane's 8 operand slots (q, e) as logical
+// index k(kk, q, e) = 32 kk + 4 q + e (e < 4) or 32 kk + 16 + 4 q + (e - 4) (e >= 4), so two
+// consecutive row tiles of one layer's output are the next layer's B operand without any data movement.
+// Weight rows are stored with their columns in that slot order ("phys" order), so an A operand is one
 // 16-byte read per part.
 //
-// Forward: each wave owns 16 NC samples and all 128 hidden units; W1 and W2 (both parts)
-// sit in LDS.  Backward: a block's waves own slices of 16 BWD_MP hidden units for the block's
-// 32-sample tiles and keep their rows of W1, W2 or W2^T in registers (two roles, see the
-// backward section); activations are exchanged through sample-major LDS planes.  The weight
-// gradients reduce over samples, so their unit-major operands are read from those planes with
-// transposing LDS reads; their accumulators carry a power-of-two frame that only ever decreases
-// (rescaled when a tile needs it), and a sample's operands are scaled so that the product lands
-// in that frame.
+// Backward: a block's waves own slices of 32 hidden units for the block's 32-sample tiles and keep their
+// rows of W1, W2 or W2^T in registers (two roles, see the backward section); activations are exchanged
+// through sample-major LDS planes.  The weight gradients reduce over samples, so their unit-major
+// operands are read from those planes with transposing LDS reads; their accumulators carry a
+// power-of-two frame that only ever decreases (rescaled when a tile needs it), and a sample's operands
+// are scaled so that the product lands in that frame.
 #include <string.h>
 
 #include "dvgo_internal.h"
@@ -166,6 +164,24 @@ __device__ __forceinline__ float group8_max(float v) {
     return fmaxf(v, dpp_movf<0x141>(v));
 }
 
+// the lower half-wave's values of a and b in the first result, the upper half-wave's in the second, each
+// a's then b's; and the same with the even and odd rows of 16 lanes
+struct Pair {
+    float a, b;
+};
+__device__ __forceinline__ Pair swap32(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    const unsigned x = r[0], y = r[1];
+    return {__builtin_bit_cast(float, x), __builtin_bit_cast(float, y)};
+}
+__device__ __forceinline__ Pair swap16(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b),
+                                                    false, false);
+    const unsigned x = r[0], y = r[1];
+    return {__builtin_bit_cast(float, x), __builtin_bit_cast(float, y)};
+}
+
 __device__ __forceinline__ float pow2(int e) { return __builtin_amdgcn_ldexpf(1.f, e); }
 __device__ __forceinline__ float ldx(float v, int e) { return __builtin_amdgcn_ldexpf(v, e); }
 
@@ -225,11 +241,13 @@ __device__ __forceinline__ int find_ray(const int *offs, int R, int s) {
 // lanes must call it.
 __device__ __forceinline__ int ray_of_group8(const int *offs, int R, int r0, int w, int sbase) {
     const int k = lane() >> 3;
-    int cnt = 0;
+    int cnt = __popcll(__ballot(w <= sbase));
+    if (cnt != __popcll(__ballot(w <= sbase + 7))) {  // not all on one ray
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int c = __popcll(__ballot(w <= sbase + i));
-        cnt = k == i ? c : cnt;
+        for (int i = 1; i < 8; ++i) {
+            const int c = __popcll(__ballot(w <= sbase + i));
+            cnt = k >= i ? c : cnt;
+        }
     }
     const int s = sbase + k;
     if (cnt == 64 && r0 + 64 <= R && offs[r0 + 64] <= s) return find_ray(offs, R, s);
@@ -762,35 +780,29 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
 
 // ------------------------------------------------------------------ backward
 //
-// Block = 2 BWD_RW waves in two roles (8 waves of 32 units each with BWD_MP = 2).  P waves
-// (0..RW-1) own units 16 BWD_MP p .. of both hidden layers for the forward recompute and hold
-// those rows of W1 and W2 in registers; C waves (RW..2RW-1) own the same units for the backward
-// chain and hold those rows of W2^T.  The C waves run one tile behind, so every phase pairs P
-// and C work on the same SIMDs.  Phases
-// of iteration t (block-wide barriers between them; the inputs of t are already staged):
-//   A  P: layer 1 of t -> h1 plane, mask bits;              C: dz1 of t-1 (frame plane)
-//         dW2 += dz2^T h1 of t-1
-//   B  P: layer 2 of t -> h2, logit partials                C: dW1 += dz1^T x of t-1, dfeat partials
-//                                                              of t-1; loads of t+1
-//   C  P: dz3, dz2 of t -> its frame plane, half of         C: dz3, exponents, b2 b3 sums, the other
-//         the dz2 plane                                        half of the dz2 plane (the same values)
-//   D  P: feature gradient of t-1                           C: stage t+1; dW3 of t; the first dz2
-//                                                              operands of dz1 of t
-// (dW2 of a tile waits for the next phase A, where the P waves would otherwise idle beside the
-// longer dz1 of the C waves; h1 is double-buffered for it, and the dz2 frame plane and the dW2
-// frame stay put until the next phase C.  The feature partials and half of the dz2 plane sit with
-// the C waves for the same balance: phase A is theirs to lengthen, phase C the P waves'.)
-// After the last tile one more A/B pair finishes the C side.  Both roles run the same
-// number of barriers, so s_barrier stays matched.
+// Block = 2 BWD_RW waves in two roles (8 waves of 32 units each).  P waves (0..RW-1) own units 32 p .. of
+// both hidden layers for the forward recompute and hold those rows of W1 and W2 in registers; C waves
+// (RW..2RW-1) own the same units for the backward chain and hold those rows of W2^T.  Two phases per
+// iteration t, with a block barrier after each:
+//   1  P: layer 1 of t -> h1 plane, mask bits;           C: dz3, exponents, dz2 of t-1 -> the dz2 plane and
+//         feature gradient of t-2; stage the inputs of      the dz2 frame plane; dW3 of t-1
+//         t+1, loads of t+2
+//   2  P: dW2 += dz2^T h1 of t-1; layer 2 of t -> h2,     C: dz1 of t-1 -> the wave's dz1 frame rows;
+//         logit partials                                    dW1 += dz1^T x, dfeat partials of t-1
+// What bounds it: registers hold two waves to a SIMD, so each wave's chains of dependent instructions show;
+// the phases therefore hold independent work of up to three tiles.  dW1 reads only frame rows that its own
+// wave wrote, so it needs no barrier of its own; the sums over three outputs (logits, dz2, dW3) go to FP32
+// matrix instructions, since the vector ALU is the busier pipe (some 800 instructions a tile and SIMD, 1,400
+// before); and the C waves, whose phase 2 is the longer, run it at a raised wave priority.  Feature, weight and
+// bias gradients of 981,504 samples: 554 us with four phases a tile, each a layer or a gradient, and the outputs'
+// sums on the vector ALU; 455 this way.
+// Both roles run the same number of barriers, so s_barrier stays matched.
 
 constexpr int BWD_MP = 2;                   // 16-unit row tiles of one layer per wave
 constexpr int BWD_RW = 8 / BWD_MP;          // waves per role: BWD_RW x 16 BWD_MP = 128 units
 constexpr int BWD_RT = 64 * BWD_RW;         // threads per role
 constexpr int BWD_WAVES = 2 * BWD_RW, BWD_THREADS = 64 * BWD_WAVES;
-// row tiles mp < DB_SPLIT of the dz2 plane are written by the P waves, the rest by the C waves
-// (both form the same dz2 values; the split balances phase C between the roles)
-constexpr int DB_SPLIT = BWD_MP / 2;
-static_assert(BWD_MP == 1 || BWD_MP == 2, "one or two row tiles per wave");
+static_assert(BWD_MP == 2 && BWD_RW == 4, "the P threads stage 8 inputs each");
 constexpr int NT = TILE;  // samples per block tile (two 16-sample column tiles)
 
 // LDS of the backward kernel (bytes); the small image part is staged at offset 0
@@ -801,23 +813,25 @@ constexpr int BSL(int img_off) { return img_off - IMG_B1; }
 // the same planes with transposing LDS reads (see tr_operand).
 constexpr int XB_BYTES = 2 * NT * RS1 * 2;           // x B operand [NT][RS1] hi, lo
 constexpr int HB_BYTES = 2 * NT * RS2 * 2;           // one [NT][RS2] hi, lo plane
-constexpr int B_XB0 = BS;                            // x: two buffers (tile parity)
-constexpr int B_HB = B_XB0 + 2 * XB_BYTES;           // h1: layer-2 and dW2 B operand, two (parity)
+constexpr int B_XB0 = BS;                            // x: three buffers (t-1, t, t+1)
+constexpr int B_HB = B_XB0 + 3 * XB_BYTES;           // h1: layer-2 and dW2 B operand, two (parity)
 constexpr int B_DB = B_HB + 2 * HB_BYTES;            // dz2: dz1 B operand (per-sample scale)
 constexpr int B_D2S = B_DB + HB_BYTES;               // dz2 in the dW2 frame: dW2 A operand
 constexpr int B_D1S = B_D2S + HB_BYTES;              // dz1 in the dW1 frame: dW1 A operand
 constexpr int B_Z3P = B_D1S + HB_BYTES;              // logit partials [RW][NT][4] f32
 constexpr int DFS = 12;                              // row of dfeat partials (features)
 constexpr int B_DFP = B_Z3P + BWD_RW * NT * 4 * 4;   // dfeat partials [RW][NT][DFS] f32
-constexpr int H2S = 36;                              // row stride (floats) of the h2 plane
-constexpr int B_H2 = B_DFP + BWD_RW * NT * DFS * 4;  // h2 [H][H2S] f32, written by P, read by C
-constexpr int B_MASK = B_H2 + H * H2S * 4;           // h1 > 0 bits per lane [2][RW waves][64 lanes] u16
-constexpr int B_XMAX = B_MASK + 2 * BWD_RW * 64 * 2; // max |x| per sample [2][NT]
-constexpr int B_GR = B_XMAX + 2 * NT * 4;            // grad_rgb [2][NT][4]
-constexpr int B_END = B_GR + 2 * NT * 16;
+constexpr int H2S = H + 4;                           // row stride (floats) of the h2 plane
+constexpr int B_H2 = B_DFP + BWD_RW * NT * DFS * 4;  // h2 [NT][H2S] f32, written by P, read by C
+constexpr int B_MASK = B_H2 + NT * H2S * 4;          // h1 > 0 bits per lane [2][RW waves][64 lanes] u16
+constexpr int B_EXP = B_MASK + 2 * BWD_RW * 64 * 2;  // exponents of x and of h1 per sample [3][NT][2]
+constexpr int B_GR = B_EXP + 3 * NT * 8;             // grad_rgb [3][NT][4]
+constexpr int B_DZ3 = B_GR + 3 * NT * 16;            // dz3 [RW waves][NT][4], each C wave its own
+constexpr int B_F2 = B_DZ3 + BWD_RW * NT * 16;       // frame of dW2
+constexpr int B_END = B_F2 + 16;
 static_assert(B_END <= 160 * 1024, "backward LDS");
 static_assert(B_XB0 % 16 == 0 && B_HB % 16 == 0 && B_DB % 16 == 0 && B_D2S % 16 == 0 && B_D1S % 16 == 0 &&
-                  B_Z3P % 16 == 0 && B_DFP % 16 == 0 && B_MASK % 8 == 0,
+                  B_Z3P % 16 == 0 && B_DFP % 16 == 0 && B_H2 % 16 == 0 && B_MASK % 8 == 0 && B_EXP % 8 == 0,
               "LDS alignment");
 
 // exponent that moves a gradient column into the accumulator frame F (operand scale e of
@@ -889,9 +903,31 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders a wave's LDS writes before its own later LDS reads of other lanes' values (the LDS keeps a wave's
+// operations in order, so this only binds the compiler).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Feature gradient of a finished tile: the partials of the C waves, summed in a fixed order; t =
 // the calling thread's index within its role.
+template <bool VEC>
 __device__ __forceinline__ void feat_grad_out(const MlpArgs &a, const float *dfp, int pbase, int t) {
+    if constexpr (VEC) {  // four features to a thread
+        const int sl = t / 3, c = 4 * (t - 3 * sl), s = pbase + sl;
+        if (sl >= NT || s >= a.S) return;
+        const float *p = dfp + sl * DFS + c;
+        float4 g = *reinterpret_cast<const float4 *>(p);
+#pragma unroll
+        for (int ww = 1; ww < BWD_RW; ++ww) {
+            const float4 v = *reinterpret_cast<const float4 *>(p + ww * NT * DFS);
+            g.x += v.x, g.y += v.y, g.z += v.z, g.w += v.w;
+        }
+        *reinterpret_cast<float4 *>(a.grad_feat + (int64_t)s * 12 + c) = g;
+        return;
+    }
     for (int i = t; i < NT * a.in_feat; i += BWD_RT) {
         const int sl = i / a.in_feat, c = i % a.in_feat;
         const int s = pbase + sl;
@@ -904,68 +940,86 @@ __device__ __forceinline__ void feat_grad_out(const MlpArgs &a, const float *dfp
     }
 }
 
-// Per-sample quantities every wave derives identically from LDS (columns c: sample 16c + j)
+// exponents of x (.x) and h1 (.y) of this lane's two samples 16c + j
 struct SampleExp {
     int ex[2], e1[2];
 };
 
-__device__ __forceinline__ SampleExp sample_exp(const float *xmax_s, const Meta &meta, int j) {
-    SampleExp r;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const float xm = xmax_s[16 * c + j];
-        r.ex[c] = scale_exp(xm);
-        r.e1[c] = scale_exp(meta.n1 * xm + meta.b1max);
-    }
-    return r;
+__device__ __forceinline__ SampleExp sample_exp(const int2 *exps, int j) {
+    const int2 a = exps[j], b = exps[16 + j];
+    return {{a.x, b.x}, {a.y, b.y}};
 }
 
-// Output-layer gradient of this lane's two samples and the exponents that follow from it.
+// Output-layer gradient of a tile and the exponents that follow from it, the same in every wave.  Lane
+// (q, j) forms output q (none for q = 3) of samples j and 16 + j, and the exponents of one sample,
+// 16 (q / 2) + j, which two swaps hand to the lanes that scale with them.
 struct GradExp {
-    float dz3[2][3];
-    int g2[2], g1[2], k2[2], k1[2];
+    float dz3[2];      // dz3[q] of sample 16c + j
+    int g2[2], g1[2];  // of sample 16c + j
+    int k2, k1;        // of sample 16 (q / 2) + j
 };
 
-__device__ __forceinline__ GradExp grad_exp(const float *z3p, const float *gr_s, const float *b3, const Meta &meta,
-                                            int j) {
+// slot of output o in a row of logit partials: the writing lanes hold outputs o and o + 2
+__device__ __forceinline__ int z3_slot(int o) { return 2 * (o & 1) + (o >> 1); }
+
+__device__ __forceinline__ GradExp grad_exp(const float *z3p, const float *gr_s, float b3q, const Meta &meta, int j,
+                                            int q) {
     GradExp g;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const int sl = 16 * c + j;
-        float mx = 0.f;
+        float z = b3q;
 #pragma unroll
-        for (int o = 0; o < 3; ++o) {
-            float z = b3[o];
-#pragma unroll
-            for (int ww = 0; ww < BWD_RW; ++ww) z += z3p[(ww * NT + sl) * 4 + o];
-            const float y = fast_sigmoid(z);
-            g.dz3[c][o] = gr_s[sl * 4 + o] * y * (1.f - y);
-            mx = fmaxf(mx, fabsf(g.dz3[c][o]));
-        }
-        // |dz2| <= n3t max|dz3| and |dz1| <= n2t |dz2| (infinity norms of W3^T and W2^T)
-        const float bnd2 = meta.n3t * mx, bnd1 = meta.n2t * bnd2;
-        g.g2[c] = scale_exp(bnd2);
-        g.g1[c] = scale_exp(bnd1);
-        g.k2[c] = bnd2 > 0.f ? ceil_exp(bnd2) : -FRAME_NONE;
-        g.k1[c] = bnd1 > 0.f ? ceil_exp(bnd1) : -FRAME_NONE;
+        for (int ww = 0; ww < BWD_RW; ++ww) z += z3p[(ww * NT + sl) * 4 + z3_slot(q)];
+        const float y = fast_sigmoid(z);
+        g.dz3[c] = gr_s[sl * 4 + q] * y * (1.f - y);  // (the fourth upstream value is zero)
     }
+    // max |dz3| over the outputs
+    const Pair h = swap32(fabsf(g.dz3[0]), fabsf(g.dz3[1]));
+    const float m = fmaxf(h.a, h.b);
+    const Pair p = swap16(m, m);
+    const float mx = fmaxf(p.a, p.b);
+    // |dz2| <= n3t max|dz3| and |dz1| <= n2t |dz2| (infinity norms of W3^T and W2^T)
+    const float bnd2 = meta.n3t * mx, bnd1 = meta.n2t * bnd2;
+    g.k2 = bnd2 > 0.f ? ceil_exp(bnd2) : -FRAME_NONE;
+    g.k1 = bnd1 > 0.f ? ceil_exp(bnd1) : -FRAME_NONE;
+    const int e2 = scale_exp(bnd2), e1 = scale_exp(bnd1);
+    const auto w2 = __builtin_amdgcn_permlane32_swap(e2, e2, false, false);
+    const auto w1 = __builtin_amdgcn_permlane32_swap(e1, e1, false, false);
+    g.g2[0] = w2[0];
+    g.g2[1] = w2[1];
+    g.g1[0] = w1[0];
+    g.g1[1] = w1[1];
     return g;
 }
 
-// (W3^T dz3) for unit row r of a lane's 4: one fixed sequence of FMAs, so both roles that form
-// it get the same value bit for bit
-__device__ __forceinline__ float w3t_dz3(const float (&wv)[3][4], const float (&dz3)[3], int r) {
-    return __builtin_fmaf(wv[2][r], dz3[2], __builtin_fmaf(wv[1][r], dz3[1], wv[0][r] * dz3[0]));
+// smallest frame the tile allows: F <= 14 + (other operand's exponent) - ceil_exp(bound), both of sample
+// 16 (q / 2) + j
+__device__ __forceinline__ int tile_frame(int other_e, int k) {
+    const int f = row16_min(14 + other_e - k);  // over the 16 samples of the row
+    // scalar, so the (rare) rescale is a real branch
+    return min(__builtin_amdgcn_readlane(f, 0), __builtin_amdgcn_readlane(f, 32));
 }
 
-// smallest frame the tile allows: F <= 14 + (other operand's exponent) - ceil_exp(bound)
-__device__ __forceinline__ int tile_frame(const int other_e[2], const int k[2]) {
-    int f = FRAME_NONE;
+// dz2 = mask(h2) W3^T dz3 of one 16-unit row tile (FP32 products, K = the three outputs): w3t = W3[q][unit j
+// of the tile], h = the lane's h2; added to db2, stored at its per-sample scale (the dz1 operand plane) and
+// in the dW2 frame
+template <bool SPLIT>
+__device__ __forceinline__ void dz2_tile(float w3t, float dz3, float4 hv, int g2, int fs, int at, unsigned char *db,
+                                         unsigned char *d2s, float (&db2)[4]) {
+    const v4f d = __builtin_amdgcn_mfma_f32_16x16x4f32(w3t, dz3, v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    const float h[4] = {hv.x, hv.y, hv.z, hv.w};
+    float dz2[4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) f = min(f, 14 + other_e[c] - k[c]);
-    f = row16_min(f);  // over the 16 sample lanes j of the row
-    // every lane holds the same value: make it scalar so the (rare) rescale is a real branch
-    return __builtin_amdgcn_readfirstlane(f);
+    for (int r = 0; r < 4; ++r) {
+        dz2[r] = h[r] > 0.f ? d[r] : 0.f;
+        db2[r] += dz2[r];
+    }
+    h4 hi, lo;
+    split4<false>(dz2, pow2(g2), hi, lo);
+    store_h4(db, 0, at, hi);
+    if (SPLIT) store_h4(db, NT * RS2 * 2, at, lo);
+    put_split4<SPLIT>(d2s, at, dz2, fs);  // exact for any shift
 }
 
 template <int M, int N>
@@ -982,7 +1036,9 @@ __device__ __forceinline__ void rescale(v4f (&acc)[M][N], int &F, int f) {
     }
 }
 
-template <bool SPLIT>
+// VEC: 12 features, feat and grad_feat 16-byte aligned (rows move as float4); a template argument, since the
+// general path's loads in one branch made the compiler wait for those of the other
+template <bool SPLIT, bool VEC>
 __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned char sm[B_END];
     copy_to_lds(sm, a.img + IMG_B1, BS);
@@ -1000,12 +1056,16 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
     float *z3p = reinterpret_cast<float *>(rB);
     float *dfp = reinterpret_cast<float *>(rB + (B_DFP - B_Z3P));
     float *h2s = reinterpret_cast<float *>(rB + (B_H2 - B_Z3P));
-    // bit (c MP + mp) 4 + r of lane (j, q) of wave w: h1 > 0 for unit 16 (MP w + mp) + 4q + r,
+    // bit 15 - ((c MP + mp) 4 + r) of lane (j, q) of wave w: h1 > 0 for unit 16 (MP w + mp) + 4q + r,
     // sample 16c + j; the P wave and the C wave of the same w use the same lane -> (unit, sample) map
     uint16_t *mask_b = reinterpret_cast<uint16_t *>(rB + (B_MASK - B_Z3P));
-    float *xmax_b = reinterpret_cast<float *>(rB + (B_XMAX - B_Z3P));
+    int2 *exp_b = reinterpret_cast<int2 *>(rB + (B_EXP - B_Z3P));
     float *gr_b = reinterpret_cast<float *>(rB + (B_GR - B_Z3P));
+    float *dz3s = reinterpret_cast<float *>(rB + (B_DZ3 - B_Z3P));
+    int *frame2 = reinterpret_cast<int *>(rB + (B_F2 - B_Z3P));
     const int ntiles = a.n_tiles;
+    // tiles blockIdx.x + t gridDim.x, t < n
+    const int n = (ntiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
     float *P = a.partial + (int64_t)blockIdx.x * a.n_params;
     float *pW1 = P, *pb1 = pW1 + H * a.n_in, *pW2 = pb1 + H, *pb2 = pW2 + H * H, *pW3 = pb2 + H, *pb3 = pW3 + 3 * H;
 
@@ -1034,41 +1094,132 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
 #pragma unroll
             for (int n = 0; n < 8; ++n) dW2[mp][n] = v4f{0.f, 0.f, 0.f, 0.f};
         int F2 = FRAME_NONE;
+        // inputs of a tile: global loads, in three steps spread over phases so that their
+        // latency overlaps other work (ray window; ray search and feature loads; staging)
+        // The loaded values stay raw until stage_tile (phase D), where lanes past the last sample
+        // and the padding columns are zeroed, so that nothing consumes the loads before then.
+        float4 xlo = make_float4(0.f, 0.f, 0.f, 0.f), xhi = xlo;
+        float grv = 0.f;
+        unsigned xok = 0;  // bit 0: xlo is real, bit 1: xhi is real, bit 2: grv is real
+        // (lane l of wave w: sample 8 w + l / 8, slot group xg = l mod 8)
+        auto load_tile = [&](int t, int r0, int win) {
+            const int ln = fresh(lane()), xg = ln & 7;
+            const int s = t * NT + 8 * w + (ln >> 3);
+            const bool sv = s < a.S;
+            // all lanes take part; this wave's samples are t NT + 8 w + (lane >> 3).  Lanes past the
+            // last sample load from the last sample and its ray (kept in range).
+            const int ray = min(ray_of_group8(a.offs, a.n_rays, r0, win, t * NT + 8 * w), a.n_rays - 1);
+            const int sc = sv ? s : a.S - 1;
+            const int kk = xg >> 2, q = xg & 3;
+            if constexpr (VEC) {
+                // every lane issues the same two 16-byte loads and one 4-byte load, with no divergent
+                // branch around them (divergent branches would make one group's loads wait for the
+                // other's, as both write the same registers)
+                const float *pe = a.pe + (int64_t)ray * PEW;
+                const float *pl = kk == 0 && q < 3 ? a.feat + (int64_t)sc * 12 + 4 * q : pe + (kk == 0 ? 0 : 20 + 4 * q);
+                xlo = *reinterpret_cast<const float4 *>(pl);
+                xhi = *reinterpret_cast<const float4 *>(pe + 4 + 4 * q);
+                grv = a.grad_rgb[(int64_t)sc * 3 + (xg < 3 ? xg : 2)];
+                xok = (sv ? 1u : 0u) | (sv && kk == 0 ? 2u : 0u) | (sv && xg < 3 ? 4u : 0u);
+            } else {
+                float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                float g = 0.f;
+                if (sv) {
+                    load_x8(a, s, ray, kk, q, v);
+                    if (xg < 3) g = a.grad_rgb[(int64_t)s * 3 + xg];
+                }
+                xlo = make_float4(v[0], v[1], v[2], v[3]);
+                xhi = make_float4(v[4], v[5], v[6], v[7]);
+                grv = g;
+                xok = 7u;
+            }
+        };
+        // ... and their split into the x plane of buffer pb (layer-1 B operand, read transposed by
+        // dW1), the sample's exponents and grad_rgb
+        auto stage_tile = [&](int xs) {
+            const int ln = fresh(lane()), xg = ln & 7, xsl = 8 * w + (ln >> 3);
+            const bool l = xok & 1u, h = xok & 2u;
+            const float xv[8] = {l ? xlo.x : 0.f, l ? xlo.y : 0.f, l ? xlo.z : 0.f, l ? xlo.w : 0.f,
+                                 h ? xhi.x : 0.f, h ? xhi.y : 0.f, h ? xhi.z : 0.f, h ? xhi.w : 0.f};
+            float m = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(xv[e]));
+            m = group8_max(m);  // over the 8 slot groups xg of this sample
+            const int ex = scale_exp(m);
+            const float sc = pow2(ex);
+            h4 h0, l0, h1, l1;
+            split4<false>(&xv[0], sc, h0, l0);
+            split4<false>(&xv[4], sc, h1, l1);
+            const int xb = B_XB0 + xs * XB_BYTES;
+            *reinterpret_cast<h8 *>(reinterpret_cast<_Float16 *>(sm + xb) + xsl * RS1 + 8 * xg) = cat(h0, h1);
+            if (SPLIT)
+                *reinterpret_cast<h8 *>(reinterpret_cast<_Float16 *>(sm + xb + NT * RS1 * 2) + xsl * RS1 + 8 * xg) =
+                    cat(l0, l1);
+            if (xg == 0) exp_b[xs * NT + xsl] = make_int2(ex, scale_exp(meta.n1 * m + meta.b1max));
+            if (xg < 4) gr_b[(xs * NT + xsl) * 4 + xg] = (xok & 4u) ? grv : 0.f;
+        };
+        // First rays of this block's tiles, 64 iterations at a time: lane l holds that of iteration
+        // wb + l (wb a multiple of 64; indices past the last tile repeat the last tile's ray, a
+        // valid ray).  One load per 64 tiles instead of a dependent load at the head of every tile.
+        auto ray_window = [&](int wb) {
+            const int t = (int)blockIdx.x + (wb + lane()) * (int)gridDim.x;
+            return a.tile_ray[t < ntiles ? t : ntiles - 1];
+        };
+        int trw = ray_window(0);
+        auto load_ahead = [&](int t, int r0, int win) { load_tile((int)blockIdx.x + t * (int)gridDim.x, r0, win); };
+        for (int t = 0; t < 2; ++t) {  // (a second tile that is not there loads the last sample, unused)
+            const int r0 = __builtin_amdgcn_readlane(trw, t);
+            load_ahead(t, r0, window_entry(a.offs, a.n_rays, r0));
+            if (t == 0) stage_tile(0);
+        }
+        lds_barrier();  // staged image and the first tile's inputs
         // dW2 += dz2^T h1 of a finished tile (K = its 32 samples; both operands read transposed from
         // the sample-major planes: the dz2 frame plane and that tile's h1 plane)
         auto dw2_step = [&](const unsigned char *h1p) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
             const int tl = tr_lane<RS2>(j, q);
+            h8 ah[BWD_MP], al[BWD_MP];
 #pragma unroll
             for (int mp = 0; mp < BWD_MP; ++mp) {
                 const int cb = unit_col(BWD_MP * w + mp);
-                const h8 ah = tr_operand<RS2>(d2s, tl, cb);
-                const h8 al = SPLIT ? tr_operand<RS2>(d2s + NT * RS2 * 2, tl, cb) : ah;
+                ah[mp] = tr_operand<RS2>(d2s, tl, cb);
+                al[mp] = SPLIT ? tr_operand<RS2>(d2s + NT * RS2 * 2, tl, cb) : ah[mp];
+            }
+            // the reads of step n + 1 beside the products of step n, and no further ahead (registers)
+            h8 bh = tr_operand<RS2>(h1p, tl, unit_col(0)), bl = SPLIT ? tr_operand<RS2>(h1p + NT * RS2 * 2, tl, unit_col(0)) : bh;
 #pragma unroll
-                for (int n = 0; n < 8; ++n) {
-                    const h8 bh = tr_operand<RS2>(h1p, tl, unit_col(n));
-                    const h8 bl = SPLIT ? tr_operand<RS2>(h1p + NT * RS2 * 2, tl, unit_col(n)) : bh;
-                    if (SPLIT) {
-                        dW2[mp][n] = mfma16(al, bh, dW2[mp][n]);
-                        dW2[mp][n] = mfma16(ah, bl, dW2[mp][n]);
-                    }
-                    dW2[mp][n] = mfma16(ah, bh, dW2[mp][n]);
+            for (int n = 0; n < 8; ++n) {
+                const h8 ch = bh, cl = bl;
+                if (n < 7) {
+                    bh = tr_operand<RS2>(h1p, tl, unit_col(n + 1));
+                    bl = SPLIT ? tr_operand<RS2>(h1p + NT * RS2 * 2, tl, unit_col(n + 1)) : bh;
                 }
+                if (SPLIT) {
+#pragma unroll
+                    for (int mp = 0; mp < BWD_MP; ++mp) dW2[mp][n] = mfma16(al[mp], ch, dW2[mp][n]);
+#pragma unroll
+                    for (int mp = 0; mp < BWD_MP; ++mp) dW2[mp][n] = mfma16(ah[mp], cl, dW2[mp][n]);
+                }
+#pragma unroll
+                for (int mp = 0; mp < BWD_MP; ++mp) dW2[mp][n] = mfma16(ah[mp], ch, dW2[mp][n]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         };
-        lds_barrier();  // staged image and the first tile's inputs
-        int it = 0;
-        for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x, ++it) {
+        int xs = 0, xn = 1;  // input buffers of t and t+1
+        for (int it = 0; it <= n; ++it) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
             const int pb = it & 1;
             unsigned char *hb = lds_region(sm, B_HB + pb * HB_BYTES);
-            const float *xmax_s = xmax_b + pb * NT;
-            const float *gr_s = gr_b + pb * NT * 4;
-            const int xb = B_XB0 + pb * XB_BYTES;
+            const int2 *exps = exp_b + xs * NT;
+            const int xb = B_XB0 + xs * XB_BYTES;
             uint16_t *mask1 = mask_b + pb * (BWD_RW * 64);
-            // ---- A: layer 1 for this wave's units; h1 -> the h1 plane, mask bits
-            {
-                const SampleExp se = sample_exp(xmax_s, meta, j);
+            // ---- 1: ray window of tile t+2 (consumed at the end of the phase)
+            if (((it + 2) & 63) == 0) trw = ray_window(it + 2);
+            const int r0n = __builtin_amdgcn_readlane(trw, (it + 2) & 63);
+            const int winn = window_entry(a.offs, a.n_rays, r0n);
+            //      layer 1 for this wave's units; h1 -> the h1 plane, mask bits
+            if (it < n) {
+                const SampleExp se = sample_exp(exps, j);
                 v4f acc[2][BWD_MP];  // [c][mp]
                 unsigned mbits = 0;
 #pragma unroll
@@ -1110,7 +1261,8 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             h1[r] = fmaxf(fmaf(acc[c][mp][r], un, bv[r]), 0.f);
-                            mbits |= (h1[r] > 0.f ? 1u : 0u) << ((c * BWD_MP + mp) * 4 + r);
+                            // shift in the sign of 0 - h1 (as integers: set unless h1 is zero)
+                            mbits = __builtin_amdgcn_alignbit(mbits, 0u - __builtin_bit_cast(unsigned, h1[r]), 31);
                         }
                         h4 hi, lo;
                         split4<false>(h1, sc, hi, lo);
@@ -1121,16 +1273,27 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                 }
                 mask1[w * 64 + ln] = (uint16_t)mbits;
             }
-            if (it > 0) dw2_step(lds_region(sm, B_HB + (pb ^ 1) * HB_BYTES));
+            //      feature gradient of the tile whose partials the last phase 2 left
+            if (it > 1) feat_grad_out<VEC>(a, dfp, ((int)blockIdx.x + (it - 2) * (int)gridDim.x) * NT, 64 * w + ln);
+            //      the next tile's inputs, loaded an iteration ago; the loads of the one after
+            if (it + 1 < n) stage_tile(xn);
+            if (it + 2 < n) load_ahead(it + 2, r0n, winn);
             lds_barrier();
-            // ---- B: layer 2 for this wave's units, logit partials
-            {
-                const SampleExp se = sample_exp(xmax_s, meta, j);
-                v4f acc[2][BWD_MP];  // [c][mp]
+            // ---- 2: dW2 of the previous tile; layer 2 for this wave's units, logit partials
+            if (it > 0) {
+                const int f = __builtin_amdgcn_readfirstlane(*frame2);  // as the dz2 frame plane was written
+                rescale(dW2, F2, f);
+                dw2_step(lds_region(sm, B_HB + (pb ^ 1) * HB_BYTES));
+            }
+            if (it < n) {
+                const SampleExp se = sample_exp(exps, j);
+                v4f acc[2][BWD_MP], zp[2];  // [c][mp]; logits of sample 16c + j over this lane's units
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+                for (int c = 0; c < 2; ++c) {
+                    zp[c] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int mp = 0; mp < BWD_MP; ++mp) acc[c][mp] = v4f{0.f, 0.f, 0.f, 0.f};
+                }
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk) {
                     h8 bh[2], bl[2];
@@ -1154,79 +1317,50 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
 #pragma unroll
                         for (int mp = 0; mp < BWD_MP; ++mp) acc[c][mp] = mfma16(w2h[mp][kk], bh[c], acc[c][mp]);
                 }
+                // W3 of output ln % 4 and this lane's units (a fourth row, never used, repeats the first)
+                float4 wa[BWD_MP];
+#pragma unroll
+                for (int mp = 0; mp < BWD_MP; ++mp)
+                    wa[mp] = *reinterpret_cast<const float4 *>(W3 + ((ln & 3) < 3 ? (ln & 3) * H : 0) +
+                                                               16 * (BWD_MP * w + mp) + 4 * q);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     const float un = pow2(-(meta.sw2 + se.e1[c]));
-                    float zp[3] = {0.f, 0.f, 0.f};
 #pragma unroll
                     for (int mp = 0; mp < BWD_MP; ++mp) {
                         const int u0 = 16 * (BWD_MP * w + mp) + 4 * q;
                         const float4 bb = *reinterpret_cast<const float4 *>(b2 + u0);
-                        const float4 x0 = *reinterpret_cast<const float4 *>(W3 + u0);
-                        const float4 x1 = *reinterpret_cast<const float4 *>(W3 + H + u0);
-                        const float4 x2 = *reinterpret_cast<const float4 *>(W3 + 2 * H + u0);
-                        const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
-                        const float wv[3][4] = {{x0.x, x0.y, x0.z, x0.w}, {x1.x, x1.y, x1.z, x1.w}, {x2.x, x2.y, x2.z, x2.w}};
+                        const float bv[4] = {bb.x, bb.y, bb.z, bb.w}, w3a[4] = {wa[mp].x, wa[mp].y, wa[mp].z, wa[mp].w};
+                        float h2[4];
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            const float h2 = fmaxf(fmaf(acc[c][mp][r], un, bv[r]), 0.f);
-                            h2s[(u0 + r) * H2S + 16 * c + j] = h2;
-#pragma unroll
-                            for (int o = 0; o < 3; ++o) zp[o] += wv[o][r] * h2;
+                            h2[r] = fmaxf(fmaf(acc[c][mp][r], un, bv[r]), 0.f);
+                            // four outputs x four samples in each of 16 blocks, this lane's unit as K
+                            zp[c] = __builtin_amdgcn_mfma_f32_4x4x1f32(w3a[r], h2[r], zp[c], 0, 0, 0);
                         }
-                    }
-#pragma unroll
-                    for (int o = 0; o < 3; ++o) {
-                        zp[o] += __shfl_xor(zp[o], 16, 64);
-                        zp[o] += __shfl_xor(zp[o], 32, 64);
-                    }
-                    const float zq = q == 0 ? zp[0] : (q == 1 ? zp[1] : zp[2]);
-                    if (q < 3) z3p[(w * NT + 16 * c + j) * 4 + q] = zq;
-                }
-            }
-            lds_barrier();
-            // ---- C: dz3, dz2 = mask(h2) W3^T dz3 (VALU): the dz2 plane and the dz2 frame plane
-            {
-                const SampleExp se = sample_exp(xmax_s, meta, j);
-                const GradExp ge = grad_exp(z3p, gr_s, b3, meta, j);
-                rescale(dW2, F2, tile_frame(se.e1, ge.k2));
-#pragma unroll
-                for (int mp = 0; mp < BWD_MP; ++mp) {
-                    const int u0 = 16 * (BWD_MP * w + mp) + 4 * q;
-                    const float4 x0 = *reinterpret_cast<const float4 *>(W3 + u0);
-                    const float4 x1 = *reinterpret_cast<const float4 *>(W3 + H + u0);
-                    const float4 x2 = *reinterpret_cast<const float4 *>(W3 + 2 * H + u0);
-                    const float wv[3][4] = {{x0.x, x0.y, x0.z, x0.w}, {x1.x, x1.y, x1.z, x1.w}, {x2.x, x2.y, x2.z, x2.w}};
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        float dz2[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float d = w3t_dz3(wv, ge.dz3[c], r);
-                            dz2[r] = h2s[(u0 + r) * H2S + 16 * c + j] > 0.f ? d : 0.f;
-                        }
-                        const int ob = (16 * c + j) * RS2 + unit_col(BWD_MP * w + mp) + 8 * q;
-                        if (mp < DB_SPLIT) {
-                            // dz2 at its per-sample scale: the dz1 operand plane (row tiles mp >=
-                            // DB_SPLIT are the C waves' share of it)
-                            h4 hi, lo;
-                            split4<false>(dz2, pow2(ge.g2[c]), hi, lo);
-                            store_h4(db, 0, ob, hi);
-                            if (SPLIT) store_h4(db, NT * RS2 * 2, ob, lo);
-                        }
-                        put_split4<SPLIT>(d2s, ob, dz2, frame_shift(F2, se.e1[c]));  // exact for any shift
+                        *reinterpret_cast<float4 *>(h2s + (16 * c + j) * H2S + u0) =
+                            make_float4(h2[0], h2[1], h2[2], h2[3]);
                     }
                 }
+                // over the four unit groups q: lane (q, j) ends with outputs q % 2 and q % 2 + 2 of sample
+                // 16 (q / 2) + j
+                float t[2][2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const Pair p = swap16(zp[c][2 * h], zp[c][2 * h + 1]);
+                        t[c][h] = p.a + p.b;
+                    }
+                const Pair p0 = swap32(t[0][0], t[1][0]), p1 = swap32(t[0][1], t[1][1]);
+                *reinterpret_cast<float2 *>(z3p + (w * NT + 16 * (q >> 1) + j) * 4 + 2 * (q & 1)) =
+                    make_float2(p0.a + p0.b, p1.a + p1.b);
             }
             lds_barrier();
-            // ---- D: feature gradient of the previous tile (its partials came from the C waves' phase A)
-            if (it > 0) feat_grad_out(a, dfp, (tile - (int)gridDim.x) * NT, tid);
-            lds_barrier();
+            xs = xn;
+            xn = xn == 2 ? 0 : xn + 1;
         }
-        // dW2 of the last tile; the C side's last A/B pair
-        if (it > 0) dw2_step(lds_region(sm, B_HB + ((it - 1) & 1) * HB_BYTES));
-        lds_barrier();
-        lds_barrier();
+        feat_grad_out<VEC>(a, dfp, ((int)blockIdx.x + (n - 1) * (int)gridDim.x) * NT, tid);
         // ---- partial gradient of the P role: W2
         const int u2 = F2 == FRAME_NONE ? 0 : -F2;
 #pragma unroll
@@ -1240,10 +1374,6 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
     } else {
         // ================================================================ C waves
         const int w = wave - BWD_RW;
-        const int ct = tid - BWD_RT;           // index within the C role
-        // input staging: the first 256 threads of the role (waves 0..3), sample xsl, slot group xg
-        const bool stager = BWD_RW <= 4 || w < 4;
-        const int xsl = ct >> 3, xg = ct & 7;
         h8 w2th[BWD_MP][4], w2tl[BWD_MP][4];
 #pragma unroll
         for (int mp = 0; mp < BWD_MP; ++mp)
@@ -1253,8 +1383,7 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                 w2th[mp][kk] = glb_h8(a.img, IMG_W2TH, o);
                 w2tl[mp][kk] = glb_h8(a.img, IMG_W2TL, o);
             }
-        // W1's feature columns, transposed (rows = features), over this wave's units as K: 32 units
-        // (two row tiles) in one 16x16x32 product, or 16 units in one 16x16x16 product
+        // W1's feature columns, transposed (rows = features), over this wave's units as K
         const int ofF = j * RS2 + unit_col(BWD_MP * w) + 8 * q;
         const h8 w1fh = glb_h8(a.img, IMG_W1FH, ofF), w1fl = glb_h8(a.img, IMG_W1FL, ofF);
         v4f dW1[BWD_MP][3];
@@ -1262,83 +1391,24 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
         for (int mp = 0; mp < BWD_MP; ++mp)
 #pragma unroll
             for (int n = 0; n < 3; ++n) dW1[mp][n] = v4f{0.f, 0.f, 0.f, 0.f};
-        // lane-local sums over this lane's samples; reduced over the 16 sample lanes at the end
-        float db1[BWD_MP][4], db2[BWD_MP][4], dw3[3][BWD_MP][4], db3[3] = {0.f, 0.f, 0.f};
+        // lane-local sums over this lane's samples; reduced over the 16 sample lanes at the end (db3 of
+        // output q)
+        float db1[BWD_MP][4], db2[BWD_MP][4], db3 = 0.f;
 #pragma unroll
         for (int mp = 0; mp < BWD_MP; ++mp)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                db1[mp][r] = db2[mp][r] = 0.f;
+            for (int r = 0; r < 4; ++r) db1[mp][r] = db2[mp][r] = 0.f;
+        // element i of dw3[g], lane l: output i, unit 32 w + 8 (l % 4) + g, samples l / 4 and 16 + l / 4
+        v4f dw3[8];
 #pragma unroll
-                for (int o = 0; o < 3; ++o) dw3[o][mp][r] = 0.f;
-            }
-        int F1 = FRAME_NONE;
-        // inputs of a tile: global loads, in three steps spread over phases so that their
-        // latency overlaps other work (ray window; ray search and feature loads; staging)
-        // The loaded values stay raw until stage_tile (phase D), where lanes past the last sample
-        // and the padding columns are zeroed, so that nothing consumes the loads before then.
-        float4 xlo = make_float4(0.f, 0.f, 0.f, 0.f), xhi = xlo;
-        float grv = 0.f;
-        unsigned xok = 0;  // bit 0: xlo is real, bit 1: xhi is real, bit 2: grv is real
-        auto load_tile = [&](int t, int r0, int win) {
-            const int s = t * NT + xsl;
-            const bool sv = s < a.S;
-            // all lanes take part; this wave's samples are t NT + 8 w + (lane >> 3).  Lanes past the
-            // last sample load from the last sample and its ray (kept in range).
-            const int ray = min(ray_of_group8(a.offs, a.n_rays, r0, win, t * NT + 8 * w), a.n_rays - 1);
-            const int sc = sv ? s : a.S - 1;
-            const int kk = xg >> 2, q = xg & 3;
-            if (a.feat_vec) {
-                // every lane issues the same two 16-byte loads and one 4-byte load, with no divergent
-                // branch around them (divergent branches would make one group's loads wait for the
-                // other's, as both write the same registers)
-                const float *pe = a.pe + (int64_t)ray * PEW;
-                const float *pl = kk == 0 && q < 3 ? a.feat + (int64_t)sc * 12 + 4 * q : pe + (kk == 0 ? 0 : 20 + 4 * q);
-                xlo = *reinterpret_cast<const float4 *>(pl);
-                xhi = *reinterpret_cast<const float4 *>(pe + 4 + 4 * q);
-                grv = a.grad_rgb[(int64_t)sc * 3 + (xg < 3 ? xg : 2)];
-                xok = (sv ? 1u : 0u) | (sv && kk == 0 ? 2u : 0u) | (sv && xg < 3 ? 4u : 0u);
-            } else {
-                float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                float g = 0.f;
-                if (sv) {
-                    load_x8(a, s, ray, kk, q, v);
-                    if (xg < 3) g = a.grad_rgb[(int64_t)s * 3 + xg];
-                }
-                xlo = make_float4(v[0], v[1], v[2], v[3]);
-                xhi = make_float4(v[4], v[5], v[6], v[7]);
-                grv = g;
-                xok = 7u;
-            }
-        };
-        // ... and their split into the x plane of buffer pb (layer-1 B operand, read transposed by
-        // dW1), max |x| and grad_rgb
-        auto stage_tile = [&](int pb) {
-            const bool l = xok & 1u, h = xok & 2u;
-            const float xv[8] = {l ? xlo.x : 0.f, l ? xlo.y : 0.f, l ? xlo.z : 0.f, l ? xlo.w : 0.f,
-                                 h ? xhi.x : 0.f, h ? xhi.y : 0.f, h ? xhi.z : 0.f, h ? xhi.w : 0.f};
-            float m = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(xv[e]));
-            m = group8_max(m);  // over the 8 slot groups xg of this sample
-            const float sc = pow2(scale_exp(m));
-            h4 h0, l0, h1, l1;
-            split4<false>(&xv[0], sc, h0, l0);
-            split4<false>(&xv[4], sc, h1, l1);
-            const int xb = B_XB0 + pb * XB_BYTES;
-            *reinterpret_cast<h8 *>(reinterpret_cast<_Float16 *>(sm + xb) + xsl * RS1 + 8 * xg) = cat(h0, h1);
-            if (SPLIT)
-                *reinterpret_cast<h8 *>(reinterpret_cast<_Float16 *>(sm + xb + NT * RS1 * 2) + xsl * RS1 + 8 * xg) =
-                    cat(l0, l1);
-            if (xg == 0) xmax_b[pb * NT + xsl] = m;
-            if (xg < 4) gr_b[(pb * NT + xsl) * 4 + xg] = (xok & 4u) ? grv : 0.f;
-        };
+        for (int g = 0; g < 8; ++g) dw3[g] = v4f{0.f, 0.f, 0.f, 0.f};
+        int F1 = FRAME_NONE, F2 = FRAME_NONE;
         // dW1 += dz1^T x of a finished tile (its x buffer pb; both operands read transposed from the
         // sample-major planes; logical inputs 0..47 in the three 16-column blocks)
-        auto dw1_step = [&](int pb) {
+        auto dw1_step = [&](int xs) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
             const int t2 = tr_lane<RS2>(j, q), t1 = tr_lane<RS1>(j, q);
-            const unsigned char *xp = lds_region(sm, B_XB0 + pb * XB_BYTES);
+            const unsigned char *xp = lds_region(sm, B_XB0 + xs * XB_BYTES);
 #pragma unroll
             for (int mp = 0; mp < BWD_MP; ++mp) {
                 const int cb = unit_col(BWD_MP * w + mp);
@@ -1356,40 +1426,24 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                 }
             }
         };
-        // dW3 += dz3 h2^T over this lane's units and samples (h2 of the current tile)
-        auto dw3_step = [&](const float (&dz3)[2][3], int j, int q) {
+        // dW3 += dz3 h2^T of the current tile for this wave's units: 4x4x1 FP32 products, a sample per block
+        // (outputs x four units), so every product is an FMA into the lane's own sum
+        auto dw3_step = [&](int ln) {
 #pragma unroll
-            for (int mp = 0; mp < BWD_MP; ++mp)
+            for (int c = 0; c < 2; ++c) {
+                const float d = dz3s[w * NT * 4 + 64 * c + ln];  // output ln % 4 of sample 16c + ln / 4
+                const float4 *hp = reinterpret_cast<const float4 *>(h2s + (16 * c + (ln >> 2)) * H2S +
+                                                                    16 * BWD_MP * w + 8 * (ln & 3));
+                const float4 h0 = hp[0], h1 = hp[1];
+                const float h[8] = {h0.x, h0.y, h0.z, h0.w, h1.x, h1.y, h1.z, h1.w};
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float h2 = h2s[(16 * (BWD_MP * w + mp) + 4 * q + r) * H2S + 16 * c + j];
-#pragma unroll
-                        for (int o = 0; o < 3; ++o) dw3[o][mp][r] += dz3[c][o] * h2;
-                    }
+                for (int g = 0; g < 8; ++g) dw3[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(d, h[g], dw3[g], 0, 0, 0);
+            }
         };
         // dz1 = mask(h1) W2^T dz2 of a tile (mask bits of parity pb, exponents g2/g1/ex of that
         // tile), dfeat partials, dz1 in the dW1 frame
-        float kdz1[BWD_MP][2][4];  // dz1 of the last dz1_step, for its feature partials
-        // The first K-step's dz2 operands and the mask bits of the next dz1_step, read at the end of
-        // phase D (the dz2 plane and the mask of that tile are complete there and stay put until the
-        // next phase C / A), so that dz1's first products do not wait for LDS at the head of phase A.
-        h8 pf_bh[2], pf_bl[2];
-        unsigned pf_mbits = 0;
-        auto dz1_prefetch = [&](int pb) {
+        auto dz1_step = [&](const int g2[2], const int g1[2], const int ex[2], unsigned mbits, float (&dz1)[BWD_MP][2][4]) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
-            pf_mbits = mask_b[pb * (BWD_RW * 64) + w * 64 + ln];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                pf_bh[c] = lds_h8(db, 0, (16 * c + j) * RS2 + 8 * q);
-                pf_bl[c] = lds_h8(db, NT * RS2 * 2, (16 * c + j) * RS2 + 8 * q);
-            }
-        };
-        auto dz1_step = [&](const int g2[2], const int g1[2], const int ex[2]) {
-            const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
-            const unsigned mbits = pf_mbits;  // this lane's h1 > 0 bits (prefetched)
-            float dz1[BWD_MP][2][4];
             v4f acc[2][BWD_MP];  // [c][mp]
 #pragma unroll
             for (int c = 0; c < 2; ++c)
@@ -1400,8 +1454,8 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                 h8 bh[2], bl[2];
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    bh[c] = kk == 0 ? pf_bh[c] : lds_h8(db, 0, (16 * c + j) * RS2 + 32 * kk + 8 * q);
-                    bl[c] = kk == 0 ? pf_bl[c] : lds_h8(db, NT * RS2 * 2, (16 * c + j) * RS2 + 32 * kk + 8 * q);
+                    bh[c] = lds_h8(db, 0, (16 * c + j) * RS2 + 32 * kk + 8 * q);
+                    bl[c] = lds_h8(db, NT * RS2 * 2, (16 * c + j) * RS2 + 32 * kk + 8 * q);
                 }
                 if (SPLIT) {
 #pragma unroll
@@ -1426,166 +1480,89 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                 for (int mp = 0; mp < BWD_MP; ++mp) {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const bool on = (mbits >> ((c * BWD_MP + mp) * 4 + r)) & 1u;
-                        dz1[mp][c][r] = on ? acc[c][mp][r] * un : 0.f;
+                        // all ones where h1 > 0
+                        int on = __builtin_amdgcn_sbfe((int)mbits, 15 - ((c * BWD_MP + mp) * 4 + r), 1);
+                        asm("" : "+v"(on));  // kept as a mask: one AND, where a select takes a compare too
+                        dz1[mp][c][r] = __builtin_bit_cast(float, __builtin_bit_cast(int, acc[c][mp][r] * un) & on);
                         db1[mp][r] += dz1[mp][c][r];
                     }
                     put_split4<SPLIT>(d1s, (16 * c + j) * RS2 + unit_col(BWD_MP * w + mp) + 8 * q, dz1[mp][c], fs);
                 }
             }
-#pragma unroll
-            for (int mp = 0; mp < BWD_MP; ++mp)
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) kdz1[mp][c][r] = dz1[mp][c][r];
         };
-        // dfeat partial of the tile whose dz1 the last dz1_step computed (kdz1; exponents g1 of that
-        // tile) over this wave's units: rows = feature 4q + r, column = sample.  It runs in phase B,
-        // where the C waves wait for the P waves' layer 2, instead of lengthening phase A.
-        auto dfeat_step = [&](const int g1[2]) {
+        // dfeat partial of that tile over this wave's units: rows = feature 4q + r, column = sample
+        auto dfeat_step = [&](const int g1[2], const float (&dz1)[BWD_MP][2][4]) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 const float sc = pow2(g1[c]);
                 v4f df = v4f{0.f, 0.f, 0.f, 0.f};
-                if constexpr (BWD_MP == 2) {
-                    h4 h0, l0, h1v, l1v;
-                    split4<true>(kdz1[0][c], sc, h0, l0);
-                    split4<true>(kdz1[1][c], sc, h1v, l1v);
-                    const h8 bh = cat(h0, h1v), bl = cat(l0, l1v);
-                    if (SPLIT) {
-                        df = mfma16(w1fl, bh, df);
-                        df = mfma16(w1fh, bl, df);
-                    }
-                    df = mfma16(w1fh, bh, df);
-                } else {
-                    // K = this wave's 16 units: slots 4q..4q+3 of the 16x16x16 product
-                    h4 h0, l0;
-                    split4<true>(kdz1[0][c], sc, h0, l0);
-                    const h4 ah = __builtin_shufflevector(w1fh, w1fh, 0, 1, 2, 3);
-                    const h4 al = __builtin_shufflevector(w1fl, w1fl, 0, 1, 2, 3);
-                    if (SPLIT) {
-                        df = __builtin_amdgcn_mfma_f32_16x16x16f16(al, h0, df, 0, 0, 0);
-                        df = __builtin_amdgcn_mfma_f32_16x16x16f16(ah, l0, df, 0, 0, 0);
-                    }
-                    df = __builtin_amdgcn_mfma_f32_16x16x16f16(ah, h0, df, 0, 0, 0);
+                h4 h0, l0, h1v, l1v;
+                split4<true>(dz1[0][c], sc, h0, l0);
+                split4<true>(dz1[1][c], sc, h1v, l1v);
+                const h8 bh = cat(h0, h1v), bl = cat(l0, l1v);
+                if (SPLIT) {
+                    df = mfma16(w1fl, bh, df);
+                    df = mfma16(w1fh, bl, df);
                 }
+                df = mfma16(w1fh, bh, df);
                 const float un = pow2(-(meta.sw1 + g1[c]));
                 if (q < DFS / 4)
                     *reinterpret_cast<float4 *>(dfp + (w * NT + 16 * c + j) * DFS + 4 * q) =
                         make_float4(df[0] * un, df[1] * un, df[2] * un, df[3] * un);
             }
         };
-        // First rays of this block's tiles, 64 iterations at a time: lane l holds that of iteration
-        // wb + l (wb a multiple of 64; indices past the last tile repeat the last tile's ray, a
-        // valid ray).  One load per 64 tiles instead of a dependent load at the head of every tile.
-        auto ray_window = [&](int wb) {
-            const int t = (int)blockIdx.x + (wb + lane()) * (int)gridDim.x;
-            return a.tile_ray[t < ntiles ? t : ntiles - 1];
-        };
-        int trw = 0;
-        if ((int)blockIdx.x < ntiles) {
-            trw = ray_window(0);
-            if (stager) {
-                const int r0 = __builtin_amdgcn_readlane(trw, 0);
-                load_tile(blockIdx.x, r0, window_entry(a.offs, a.n_rays, r0));
-                stage_tile(0);
-            }
-        }
         lds_barrier();  // staged image and the first tile's inputs
-        int it = 0, pbase = -1;
-        int pg2[2] = {0, 0}, pg1[2] = {0, 0}, pex[2] = {0, 0};  // exponents of the previous tile
-        float tdz3[2][3];                                         // this tile's dz3 (for dW3 in D)
-        for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x, ++it) {
+        // W3 as the operand of dz2: output q of unit j of a row tile
+        const float w3t[BWD_MP] = {q < 3 ? W3[q * H + 16 * BWD_MP * w + j] : 0.f,
+                                   q < 3 ? W3[q * H + 16 * (BWD_MP * w + 1) + j] : 0.f};
+        const float b3q = b3[q];
+        int xs = 0, xp = 2;  // input buffers of t and t-1
+        for (int it = 0; it <= n; ++it) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
-            const int pb = it & 1;
-            const bool next = tile + (int)gridDim.x < ntiles;
-            // ---- A: ray window of the next tile (its loads are issued first and consumed in B);
-            //      dz1 of the previous tile
-            if (((it + 1) & 63) == 0) trw = ray_window(it + 1);
-            const int r0n = __builtin_amdgcn_readlane(trw, (it + 1) & 63);
-            const int winn = window_entry(a.offs, a.n_rays, r0n);
-            if (pbase >= 0) dz1_step(pg2, pg1, pex);
-            lds_barrier();
-            // ---- B: dW1 of the previous tile; then the loads of the next tile's inputs, whose
-            //      latency runs through phase C (they are staged in D)
-            if (pbase >= 0) {
-                dw1_step(pb ^ 1);
-                dfeat_step(pg1);
-            }
-            if (stager) load_tile(tile + gridDim.x, r0n, winn);  // past the last tile: zeroed, not staged
-            lds_barrier();
-            // ---- C: output gradient and exponents of this tile; the frame of dW1; db2 += dz2,
-            //      db3 += dz3 (VALU, h2 from the P waves)
-            {
-                const SampleExp se = sample_exp(xmax_b + pb * NT, meta, j);
-                const GradExp ge = grad_exp(z3p, gr_b + pb * NT * 4, b3, meta, j);
-                rescale(dW1, F1, tile_frame(se.ex, ge.k1));
+            int g2[2] = {0, 0}, g1[2] = {0, 0}, ex[2] = {0, 0};  // exponents of the previous tile
+            __builtin_amdgcn_s_setprio(0);
+            // ---- 1: output gradient and exponents of the previous tile, the frames, db3 += dz3; dz2; dW3
+            if (it > 0) {
+                const SampleExp se = sample_exp(exp_b + xp * NT, j);
+                const GradExp ge = grad_exp(z3p, gr_b + xp * NT * 4, b3q, meta, j, q);
+                rescale(dW1, F1, tile_frame(q < 2 ? se.ex[0] : se.ex[1], ge.k1));
+                F2 = min(F2, tile_frame(q < 2 ? se.e1[0] : se.e1[1], ge.k2));
+                if (tid == BWD_RT) *frame2 = F2;
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    pg2[c] = ge.g2[c];
-                    pg1[c] = ge.g1[c];
-                    pex[c] = se.ex[c];
-#pragma unroll
-                    for (int o = 0; o < 3; ++o) tdz3[c][o] = ge.dz3[c][o];
+                    g2[c] = ge.g2[c];
+                    g1[c] = ge.g1[c];
+                    ex[c] = se.ex[c];
+                    db3 += ge.dz3[c];
+                    dz3s[(w * NT + 16 * c + j) * 4 + q] = ge.dz3[c];
                 }
-                if (w == 0 && q == 0) {
+                wave_lds_fence();
 #pragma unroll
-                    for (int c = 0; c < 2; ++c)
-#pragma unroll
-                        for (int o = 0; o < 3; ++o) db3[o] += ge.dz3[c][o];
-                }
-#pragma unroll
-                for (int mp = 0; mp < BWD_MP; ++mp) {
-                    const int u0 = 16 * (BWD_MP * w + mp) + 4 * q;
-                    const float4 x0 = *reinterpret_cast<const float4 *>(W3 + u0);
-                    const float4 x1 = *reinterpret_cast<const float4 *>(W3 + H + u0);
-                    const float4 x2 = *reinterpret_cast<const float4 *>(W3 + 2 * H + u0);
-                    const float wv[3][4] = {{x0.x, x0.y, x0.z, x0.w}, {x1.x, x1.y, x1.z, x1.w}, {x2.x, x2.y, x2.z, x2.w}};
+                for (int mp = 0; mp < BWD_MP; ++mp)
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        float dz2[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float h2 = h2s[(u0 + r) * H2S + 16 * c + j];
-                            const float d = w3t_dz3(wv, ge.dz3[c], r);
-                            dz2[r] = h2 > 0.f ? d : 0.f;  // the P waves' dz2, bit for bit
-                            db2[mp][r] += dz2[r];
-                        }
-                        // dz2 at its per-sample scale, the B operand of the next phase A's dz1: row
-                        // tiles mp >= DB_SPLIT (the P waves write the others)
-                        if (mp >= DB_SPLIT) {
-                            h4 hi, lo;
-                            split4<false>(dz2, pow2(ge.g2[c]), hi, lo);
-                            const int ob = (16 * c + j) * RS2 + unit_col(BWD_MP * w + mp) + 8 * q;
-                            store_h4(db, 0, ob, hi);
-                            if (SPLIT) store_h4(db, NT * RS2 * 2, ob, lo);
-                        }
+                        const float4 hv = *reinterpret_cast<const float4 *>(h2s + (16 * c + j) * H2S +
+                                                                            16 * (BWD_MP * w + mp) + 4 * q);
+                        dz2_tile<SPLIT>(w3t[mp], ge.dz3[c], hv, ge.g2[c], frame_shift(F2, se.e1[c]),
+                                        (16 * c + j) * RS2 + unit_col(BWD_MP * w + mp) + 8 * q, db, d2s, db2[mp]);
                     }
-                }
+                dw3_step(ln);
             }
             lds_barrier();
-            // ---- D: the next tile's inputs -> x planes (the P waves write the previous tile's
-            //      feature gradient meanwhile); dW3 += dz3 h2^T of this tile (h2 stays until the
-            //      P waves' next layer 2)
-            if (next && stager) stage_tile(pb ^ 1);
-            dw3_step(tdz3, j, q);
-            dz1_prefetch(pb);  // for the next phase A's dz1 of this tile
+            // ---- 2: dz1, dW1 and dfeat of the previous tile
+            __builtin_amdgcn_s_setprio(3);  // (490 -> 473 us)
+            if (it > 0) {
+                float dz1[BWD_MP][2][4];
+                dz1_step(g2, g1, ex, mask_b[((it - 1) & 1) * (BWD_RW * 64) + w * 64 + ln], dz1);
+                wave_lds_fence();
+                dw1_step(xp);
+                dfeat_step(g1, dz1);
+            }
             lds_barrier();
-            pbase = tile * NT;
+            xp = xs;
+            xs = xs == 2 ? 0 : xs + 1;
         }
-        // ---- the last tile: A (dz1), B (dW1 and the feature gradient)
-        if (pbase >= 0) {
-            dz1_step(pg2, pg1, pex);  // operands prefetched in the last phase D
-            dfeat_step(pg1);  // before the barrier: feat_grad_out below reads every wave's partials
-        }
-        lds_barrier();
-        if (pbase >= 0) {
-            dw1_step((it - 1) & 1);
-            feat_grad_out(a, dfp, pbase, ct);
-        }
-        lds_barrier();
         // ---- partial gradients of the C role: W1, b1, b2, W3, b3
         const int u1 = F1 == FRAME_NONE ? 0 : -F1;
 #pragma unroll
@@ -1598,26 +1575,29 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                     const int c = w1_col(a.in_feat, a.n_freq, 16 * n + j);
                     if (c >= 0) pW1[hrow * a.n_in + c] = ldx(dW1[mp][n][r], u1);
                 }
-                float s1 = db1[mp][r], s2 = db2[mp][r], s3[3] = {dw3[0][mp][r], dw3[1][mp][r], dw3[2][mp][r]};
+                float s1 = db1[mp][r], s2 = db2[mp][r];
 #pragma unroll
                 for (int o = 1; o < 16; o <<= 1) {
                     s1 += __shfl_xor(s1, o, 64);
                     s2 += __shfl_xor(s2, o, 64);
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) s3[t] += __shfl_xor(s3[t], o, 64);
                 }
                 if (j == 0) {
                     pb1[hrow] = s1;
                     pb2[hrow] = s2;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) pW3[t * H + hrow] = s3[t];
                 }
             }
 #pragma unroll
-        for (int o = 1; o < 16; o <<= 1)
+        for (int g = 0; g < 8; ++g)
 #pragma unroll
-            for (int t = 0; t < 3; ++t) db3[t] += __shfl_xor(db3[t], o, 64);
-        if (ct < 3) pb3[ct] = db3[ct];
+            for (int i = 0; i < 3; ++i) {
+                float s3 = dw3[g][i];
+#pragma unroll
+                for (int o = 4; o < 64; o <<= 1) s3 += __shfl_xor(s3, o, 64);
+                if (ln < 4) pW3[i * H + 16 * BWD_MP * w + 8 * ln + g] = s3;
+            }
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) db3 += __shfl_xor(db3, o, 64);
+        if (w == 0 && j == 0 && q < 3) pb3[q] = db3;
     }
 }
 
@@ -1829,10 +1809,18 @@ int mlp_backward_impl(const dvgo_color_mlp *m, int32_t n_rays, const int32_t *ra
         rc = launch_prep(a, st);
         if (rc) return rc;
     }
-    if (m->precision == DVGO_MLP_F16)
-        hipLaunchKernelGGL((mlp_bwd_kernel<false>), dim3(a.nblocks), dim3(BWD_THREADS), 0, st, a);
-    else
-        hipLaunchKernelGGL((mlp_bwd_kernel<true>), dim3(a.nblocks), dim3(BWD_THREADS), 0, st, a);
+    const bool vec = a.feat_vec && ((uintptr_t)grad_feat & 15) == 0;
+    const dim3 grid(a.nblocks), block(BWD_THREADS);
+    if (m->precision == DVGO_MLP_F16) {
+        if (vec)
+            hipLaunchKernelGGL((mlp_bwd_kernel<false, true>), grid, block, 0, st, a);
+        else
+            hipLaunchKernelGGL((mlp_bwd_kernel<false, false>), grid, block, 0, st, a);
+    } else if (vec) {
+        hipLaunchKernelGGL((mlp_bwd_kernel<true, true>), grid, block, 0, st, a);
+    } else {
+        hipLaunchKernelGGL((mlp_bwd_kernel<true, false>), grid, block, 0, st, a);
+    }
     rc = check_hip(hipGetLastError(), "mlp_bwd_kernel launch");
     if (rc || !reduce) return rc;
     return launch_reduce(a, st);
