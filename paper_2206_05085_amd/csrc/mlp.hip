@@ -793,9 +793,9 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
 // the phases therefore hold independent work of up to three tiles.  dW1 reads only frame rows that its own
 // wave wrote, so it needs no barrier of its own; the sums over three outputs (logits, dz2, dW3) go to FP32
 // matrix instructions, since the vector ALU is the busier pipe (some 800 instructions a tile and SIMD, 1,400
-// before); and the C waves, whose phase 2 is the longer, run it at a raised wave priority.  Feature, weight and
+// before); and the C waves run dz1, the longest chain of phase 2, at a raised wave priority.  Feature, weight and
 // bias gradients of 981,504 samples: 554 us with four phases a tile, each a layer or a gradient, and the outputs'
-// sums on the vector ALU; 455 this way.
+// sums on the vector ALU; 440 this way.
 // Both roles run the same number of barriers, so s_barrier stays matched.
 
 constexpr int BWD_MP = 2;                   // 16-unit row tiles of one layer per wave
@@ -1521,7 +1521,6 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
         for (int it = 0; it <= n; ++it) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
             int g2[2] = {0, 0}, g1[2] = {0, 0}, ex[2] = {0, 0};  // exponents of the previous tile
-            __builtin_amdgcn_s_setprio(0);
             // ---- 1: output gradient and exponents of the previous tile, the frames, db3 += dz3; dz2; dW3
             if (it > 0) {
                 const SampleExp se = sample_exp(exp_b + xp * NT, j);
@@ -1551,13 +1550,16 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
             }
             lds_barrier();
             // ---- 2: dz1, dW1 and dfeat of the previous tile
-            __builtin_amdgcn_s_setprio(3);  // (490 -> 473 us)
             if (it > 0) {
+                __builtin_amdgcn_s_setprio(3);  // 490 -> 473 us
                 float dz1[BWD_MP][2][4];
                 dz1_step(g2, g1, ex, mask_b[((it - 1) & 1) * (BWD_RW * 64) + w * 64 + ln], dz1);
+                // the raised priority is for the chain up to here, and the feature partials cover the way of
+                // the frame rows through LDS: 457 -> 440 us
+                __builtin_amdgcn_s_setprio(0);
                 wave_lds_fence();
-                dw1_step(xp);
                 dfeat_step(g1, dz1);
+                dw1_step(xp);
             }
             lds_barrier();
             xp = xs;
