@@ -174,7 +174,7 @@ struct OwnArgs {
 // tile (thread = pair; LDS atomics, corners visited in a lane-rotated order so that neighbouring
 // lanes holding samples of one cell add to different vertices in the same instruction); then every
 // touched vertex is written once.  The LDS atomics cost grows with the channel count: this is the
-// density's scatter (one channel); the 12-channel features keep the in-wave aggregated global
+// density's scatter (one channel); the 12-channel features keep the slot walks and global
 // atomics of dvgo_grid_scatter.
 template <int NC, bool W, int MODE>
 __global__ __launch_bounds__(OWN_THREADS) void own_scatter_kernel(OwnArgs A) {

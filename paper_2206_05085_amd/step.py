@@ -33,12 +33,12 @@ class TrainStep:
         ops.WARP_CONTRACT_L2) and the batch holds world points.  mlp_precision: ops.MLP_SPLIT_F16
         (FP32-grade colour head) or ops.MLP_F16 (the cheaper head, FP16 matrix operands).
         binned_scatter: the renderer writes per-sample density gradients, which are scattered
-        brick by brick (samples binned once per step) instead of by in-wave aggregated atomics
+        brick by brick (samples binned once per step) instead of by the atomic scatter
         inside the render kernel.  owner_scatter (with binned_scatter; off by default, the step measured
         about 1% slower with it): the density gradient is summed by the 4x4x32-vertex bricks that own the vertices (no global atomics), and when no TV
         term joins it, the density's Adam update is fused into that sum (its gradient never reaches
         memory); without it the density uses the atomic brick scatter.  The 12-channel feature
-        gradient always takes the in-wave aggregated atomic scatter and the streaming Adam (the
+        gradient always takes the atomic scatter along the rays and the streaming Adam (the
         owner sum of 12 channels measured slower).  concurrent: in the feature-grid mode, run the binning, the
         density scatter, the density and MLP Adam updates and the colour head's preparation for
         the next step on a second stream, overlapped with the feature scatter and feature Adam
@@ -250,7 +250,7 @@ class TrainStep:
             ops.grid_scatter_binned(self.grid("density"), b.xyz, self.g_raw, self.bin_ws)
 
     def _scatter_feat(self):
-        # the 12-channel feature gradient keeps the in-wave aggregated atomic scatter (owner-brick sums
+        # the 12-channel feature gradient keeps the atomic scatter along the rays (owner-brick sums
         # of 12 channels measured slower)
         ops.grid_scatter(self.grid("feat"), self.batch.xyz, self.g_feat_s)
 
