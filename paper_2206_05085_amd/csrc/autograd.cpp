@@ -13,6 +13,7 @@
 
 #include <array>
 #include <optional>
+#include <string>
 #include <vector>
 
 #include "dvgo.h"
@@ -31,6 +32,29 @@ bool fits(const Tensor &t, at::ScalarType dt = at::kFloat) {
     return t.defined() && t.is_cuda() && t.layout() == at::kStrided && t.scalar_type() == dt && t.is_contiguous();
 }
 bool fits(const Tensor &t, int64_t numel, at::ScalarType dt = at::kFloat) { return fits(t, dt) && t.numel() == numel; }
+
+std::string dtype_of(const Tensor &t) {
+    pybind11::gil_scoped_acquire gil;
+    return pybind11::str(pybind11::cast(t).attr("dtype"));
+}
+
+// The checks of a backward on what it hands to the library, with the Python path's errors.  A tensor that
+// comes back from a saved-tensor hook has the values, the sizes, the type and the device of the one that
+// went in, if the hook keeps to its contract, but not its strides; and not every hook keeps to it.
+void expect(const Tensor &t, const char *name, at::ScalarType dt = at::kFloat) {
+    TORCH_CHECK_VALUE(t.defined() && t.is_cuda(), name, " must live on the GPU (libdvgo has no CPU path)");
+    TORCH_CHECK_TYPE(t.scalar_type() == dt, name, " must be ",
+                     dt == at::kFloat ? "torch.float32" : (dt == at::kInt ? "torch.int32" : "torch.uint8"), ", got ", dtype_of(t));
+    TORCH_CHECK_VALUE(t.layout() == at::kStrided && t.has_storage() && t.is_contiguous(), name, " must be contiguous");
+}
+void expect(const Tensor &t, const char *name, int64_t numel, at::ScalarType dt = at::kFloat) {
+    expect(t, name, dt);
+    TORCH_CHECK_VALUE(t.numel() == numel, name, " has ", t.numel(), " elements, expected ", numel);
+}
+void expect_grid(const Tensor &t) {
+    expect(t, "grid data");
+    TORCH_CHECK_VALUE(t.dim() == 4, "grid data must be [nx, ny, nz, ch_stride]");
+}
 
 // the library said no although the forward had gone through
 void check(int rc, const char *fn) {
@@ -75,6 +99,13 @@ struct RenderCall : torch::CustomClassHolder {
     Vec3 bg;
     bool refused = false;  // the forward found that the library does not take the call
 
+    void expect_samples() const {
+        expect(offs, "ray_offsets", n_rays + 1, at::kInt);
+        expect(xyz, "xyz", 3 * n_samples);
+        expect(delta, "delta", n_samples);
+        expect(s_mid, "s_mid", n_samples);
+        expect(s_len, "s_len", n_samples);
+    }
     dvgo_samples samples() const {
         return {sizeof(dvgo_samples), (int32_t)n_rays, n_samples, offs.data_ptr<int32_t>(), f(xyz), f(delta), f(s_mid), f(s_len)};
     }
@@ -117,6 +148,12 @@ struct RenderNode : torch::autograd::Function<RenderNode> {
         const auto saved = ctx->get_saved_variables();
         const Tensor &density = saved[0], &colour = saved[1], &T = saved[2], &state = saved[3];
         const auto c = c10::static_intrusive_pointer_cast<RenderCall>(ctx->saved_data["call"].toCapsule());
+        c->expect_samples();
+        expect_grid(density);
+        if (c->grid_color) expect_grid(colour);
+        else expect(colour, "sample_rgb", 3 * c->n_samples);
+        expect(T, "T_final", c->n_rays);
+        expect(state, "state", at::kByte);
         const Tensor g_rgb = g[0].defined() ? g[0].contiguous() : at::zeros({c->n_rays, 3}, T.options());
         const Tensor g_T = g[1].defined() ? g[1].contiguous() : Tensor();
         const Tensor g_dist = g[2].defined() && c->want_dist ? g[2].contiguous() : Tensor();
@@ -179,6 +216,10 @@ struct DistortionNode : torch::autograd::Function<DistortionNode> {
         const auto saved = ctx->get_saved_variables();
         const Tensor w = saved[0].contiguous(), &offs = saved[1], &sm = saved[2], &sl = saved[3];
         if (!g[0].defined()) return {Tensor(), Tensor(), Tensor(), Tensor(), Tensor()};
+        expect(offs, "ray_offsets", at::kInt);
+        expect(w, "w");
+        expect(sm, "s_mid", w.numel());
+        expect(sl, "s_len", w.numel());
         const int32_t R = (int32_t)(offs.numel() - 1);
         size_t need = 0;
         check(dvgo_distortion_workspace_size(R, w.numel(), &need), "dvgo_distortion_workspace_size");
@@ -224,6 +265,8 @@ struct GatherNode : torch::autograd::Function<GatherNode> {
         const Tensor &grid = saved[0], &xyz = saved[1];
         const auto c = c10::static_intrusive_pointer_cast<BoxCall>(ctx->saved_data["call"].toCapsule());
         if (!g[0].defined()) return {Tensor(), Tensor(), Tensor()};
+        expect_grid(grid);
+        expect(xyz, "xyz", g[0].size(0) * 3);
         const Tensor gg = at::zeros_like(grid), go = g[0].contiguous();
         const dvgo_grid dg = grid_of(grid, c->lo, c->hi, 0, gg);
         check(dvgo_grid_scatter(&dg, xyz.numel() / 3, f(xyz), f(go), stream()), "dvgo_grid_scatter");
@@ -301,6 +344,13 @@ struct HeadNode : torch::autograd::Function<HeadNode> {
         if (!g[0].defined()) return variable_list(10);
         const Tensor &feat = v[0], &offs = v[7], &dirs = v[8];
         const Tensor W[3] = {v[1], v[3], v[5]}, b[3] = {v[2], v[4], v[6]};
+        for (int i = 0; i < 3; ++i) {
+            expect(W[i], ("W" + std::to_string(i + 1)).c_str());
+            expect(b[i], ("b" + std::to_string(i + 1)).c_str());
+        }
+        expect(feat, "feat");
+        expect(offs, "ray_offsets", at::kInt);
+        expect(dirs, "dirs", 3 * (offs.numel() - 1));
         Tensor gW[3], gb[3];
         std::vector<Tensor> all;
         for (int i = 0; i < 3; ++i) {
