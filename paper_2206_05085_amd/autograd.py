@@ -13,6 +13,7 @@ Functions, 40 us of it on the GPU).
 from __future__ import annotations
 
 import torch
+from torch.autograd import forward_ad
 
 from . import ops
 
@@ -37,8 +38,10 @@ def _native():
 
 def _eager(*tensors) -> bool:
     """Whether a call may take a C++ node: plain CUDA tensors, and nothing around it that looks into an
-    autograd.Function (function transforms, tracing, compilation, dispatch modes), which a node passes by."""
+    autograd.Function (function transforms, forward-mode differentiation, tracing, compilation, dispatch modes),
+    which a node passes by."""
     return (all(type(t) in _PLAIN and t.is_cuda for t in tensors) and not torch._C._are_functorch_transforms_active()
+            and forward_ad._current_level < 0
             and torch._C._get_tracing_state() is None and not torch._C._len_torch_dispatch_stack()
             and not torch.compiler.is_compiling())
 

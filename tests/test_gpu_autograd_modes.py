@@ -1,0 +1,43 @@
+"""The autograd entry points under the modes and call forms that their Functions serve (GPU)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from test_gpu_autograd_nodes import KINDS, _call  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _first(out):
+    return out[0] if isinstance(out, (tuple, list)) else out
+
+
+def _outcome(fn):
+    try:
+        return fn()
+    except Exception as e:  # noqa: BLE001
+        return type(e), str(e)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_forward_mode_takes_the_function(kind):
+    from torch.autograd import forward_ad
+
+    from paper_2206_05085_amd import autograd as mod
+
+    def dual(node):
+        fn, leaves = _call(kind, mod, node)
+        with forward_ad.dual_level():
+            return fn(forward_ad.make_dual(leaves[0], torch.ones_like(leaves[0])), *leaves[1:])
+
+    def plain(node):  # a level is active, but no tensor has a tangent
+        fn, leaves = _call(kind, mod, node)
+        with forward_ad.dual_level():
+            out = _first(fn(*[t.requires_grad_() for t in leaves]))
+        return out, type(out.grad_fn).__name__
+
+    print("[case] forward mode", kind, flush=True)
+    want = _outcome(lambda: dual(False))
+    assert want[0] is NotImplementedError and _outcome(lambda: dual(True)) == want
+    (x, name), (y, want) = plain(True), plain(False)
+    assert name == want and torch.equal(x, y)
