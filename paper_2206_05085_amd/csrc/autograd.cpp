@@ -138,7 +138,7 @@ struct RenderNode : torch::autograd::Function<RenderNode> {
                                      f(T), c->want_dist ? f(dist) : nullptr, nullptr, state.data_ptr(), need, stream());
         c->refused = rc != DVGO_OK;
         if (!c->want_dist && !c->refused) dist.zero_();
-        ctx->set_materialize_grads(false);
+        ctx->set_materialize_grads(false);  // three outputs: the backward knows what to leave out
         ctx->save_for_backward({density, colour, T, state});
         ctx->saved_data["call"] = c10::IValue::make_capsule(c);
         return {rgb, T, dist};
@@ -208,14 +208,12 @@ struct DistortionNode : torch::autograd::Function<DistortionNode> {
         const Tensor wc = w.contiguous(), loss = floats({offs.numel() - 1}, w);
         *refused = dvgo_distortion_loss((int32_t)(offs.numel() - 1), offs.data_ptr<int32_t>(), wc.numel(), f(wc), f(sm), f(sl),
                                         f(loss), nullptr, nullptr, nullptr, 0, stream()) != DVGO_OK;
-        ctx->set_materialize_grads(false);
         ctx->save_for_backward({w, offs, sm, sl});
         return loss;
     }
     static variable_list backward(AutogradContext *ctx, variable_list g) {
         const auto saved = ctx->get_saved_variables();
         const Tensor w = saved[0].contiguous(), &offs = saved[1], &sm = saved[2], &sl = saved[3];
-        if (!g[0].defined()) return {Tensor(), Tensor(), Tensor(), Tensor(), Tensor()};
         expect(offs, "ray_offsets", at::kInt);
         expect(w, "w");
         expect(sm, "s_mid", w.numel());
@@ -255,7 +253,6 @@ struct GatherNode : torch::autograd::Function<GatherNode> {
         const Tensor out = floats({S, grid.size(3)}, xyz);
         const dvgo_grid g = grid_of(grid, c->lo, c->hi, 0);
         c->refused = dvgo_grid_gather(&g, S, f(xyz), f(out), stream()) != DVGO_OK;
-        ctx->set_materialize_grads(false);
         ctx->save_for_backward({grid, xyz});
         ctx->saved_data["call"] = c10::IValue::make_capsule(c);
         return out;
@@ -264,7 +261,6 @@ struct GatherNode : torch::autograd::Function<GatherNode> {
         const auto saved = ctx->get_saved_variables();
         const Tensor &grid = saved[0], &xyz = saved[1];
         const auto c = c10::static_intrusive_pointer_cast<BoxCall>(ctx->saved_data["call"].toCapsule());
-        if (!g[0].defined()) return {Tensor(), Tensor(), Tensor()};
         expect_grid(grid);
         expect(xyz, "xyz", g[0].size(0) * 3);
         const Tensor gg = at::zeros_like(grid), go = g[0].contiguous();
@@ -333,7 +329,6 @@ struct HeadNode : torch::autograd::Function<HeadNode> {
             rc = dvgo_mlp_forward(&m, R, offs.data_ptr<int32_t>(), f(dirs), S, f(feat), f(rgb), ws.data_ptr(), need, stream());
         }
         c->refused = rc != DVGO_OK;
-        ctx->set_materialize_grads(false);
         ctx->save_for_backward({feat, W1, b1, W2, b2, W3, b3, offs, dirs});
         ctx->saved_data["call"] = c10::IValue::make_capsule(c);
         return rgb;
@@ -341,7 +336,6 @@ struct HeadNode : torch::autograd::Function<HeadNode> {
     static variable_list backward(AutogradContext *ctx, variable_list g) {
         const auto v = ctx->get_saved_variables();
         const auto c = c10::static_intrusive_pointer_cast<HeadCall>(ctx->saved_data["call"].toCapsule());
-        if (!g[0].defined()) return variable_list(10);
         const Tensor &feat = v[0], &offs = v[7], &dirs = v[8];
         const Tensor W[3] = {v[1], v[3], v[5]}, b[3] = {v[2], v[4], v[6]};
         for (int i = 0; i < 3; ++i) {

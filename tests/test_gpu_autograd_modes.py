@@ -41,3 +41,28 @@ def test_forward_mode_takes_the_function(kind):
     assert want[0] is NotImplementedError and _outcome(lambda: dual(True)) == want
     (x, name), (y, want) = plain(True), plain(False)
     assert name == want and torch.equal(x, y)
+
+
+class _NoGradient(torch.autograd.Function):
+    """A consumer whose backward has nothing to pass on."""
+
+    @staticmethod
+    def forward(ctx, x):
+        return x.clone()
+
+    @staticmethod
+    def backward(ctx, g):
+        return None
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_undefined_upstream_gradients_are_zeros(kind):
+    from paper_2206_05085_amd import autograd as mod
+    print("[case] undefined upstream", kind, flush=True)
+    for node in (True, False):
+        fn, leaves = _call(kind, mod, node)
+        leaves = [t.requires_grad_() for t in leaves]
+        out = fn(*leaves)
+        out = list(out) if isinstance(out, (tuple, list)) else [out]
+        grads = torch.autograd.grad(sum(_NoGradient.apply(o).sum() for o in out), leaves)
+        assert all(g.shape == t.shape and not g.any() for g, t in zip(grads, leaves)), node
