@@ -8,6 +8,7 @@
 // what the Python path checks and returns None where a check or the library refuses the call, so that the
 // Python path then raises its own error for it; it never launches in that case.
 #include <torch/extension.h>
+#include <torch/csrc/Exceptions.h>
 
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
 
@@ -56,9 +57,16 @@ void expect_grid(const Tensor &t) {
     TORCH_CHECK_VALUE(t.dim() == 4, "grid data must be [nx, ny, nz, ch_stride]");
 }
 
-// the library said no although the forward had gone through
+// the library said no although the forward had gone through: the binding's DvgoError, with its code
 void check(int rc, const char *fn) {
-    TORCH_CHECK(rc == DVGO_OK, fn, " failed with ", rc, ": ", dvgo_last_error());
+    if (rc == DVGO_OK) return;
+    const std::string detail = dvgo_last_error();
+    pybind11::gil_scoped_acquire gil;
+    const pybind11::object type = pybind11::module_::import("paper_2206_05085_amd._lib").attr("DvgoError");
+    PyErr_SetObject(type.ptr(), type(fn, rc, detail).ptr());
+    python_error e;
+    e.persist();
+    throw e;
 }
 
 Tensor floats(at::IntArrayRef shape, const Tensor &like) { return at::empty(shape, like.options().dtype(at::kFloat)); }

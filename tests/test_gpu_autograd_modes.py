@@ -66,3 +66,31 @@ def test_undefined_upstream_gradients_are_zeros(kind):
         out = list(out) if isinstance(out, (tuple, list)) else [out]
         grads = torch.autograd.grad(sum(_NoGradient.apply(o).sum() for o in out), leaves)
         assert all(g.shape == t.shape and not g.any() for g, t in zip(grads, leaves)), node
+
+
+def test_library_errors_of_a_backward_are_dvgo_errors():
+    # a batch spoilt after the forward, which debug mode finds on the device before anything is launched
+    from paper_2206_05085_amd import _lib, autograd as mod, ops
+    import synth
+    wl = synth.config2(R=40, N=48, n=24)
+    smp = wl.samples
+    errors = []
+    for node in (True, False):
+        b = ops.SampleBatch.from_arrays(smp.ray_offsets, smp.xyz, smp.delta, smp.s_mid.copy(), smp.s_len)
+        d = torch.as_tensor(wl.density.data).cuda().requires_grad_()
+        c = torch.rand(smp.n_samples, 3, device="cuda")
+        box = (wl.density.xyz_min, wl.density.xyz_max)
+        before = ops.set_debug(True)
+        try:
+            args = (False, -4.0, 0.0, (1.0, 1.0, 1.0), True)
+            if node:
+                out = mod.render(d, c, b, box, grid_color=args[0], act_shift=args[1])
+            else:
+                out = mod.RenderFn.apply(d, c, b, box, *args)
+            b.s_mid.copy_(b.s_mid.flip(0))
+            with pytest.raises(_lib.DvgoError) as e:
+                out[0].sum().backward()
+            errors.append((e.value.code, str(e.value)))
+        finally:
+            ops.set_debug(before)
+    assert errors[0] == errors[1] and _lib.ERRORS[errors[0][0]] == "ERR_UNSORTED"
