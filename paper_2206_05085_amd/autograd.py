@@ -46,6 +46,11 @@ def _eager(*tensors) -> bool:
             and not torch.compiler.is_compiling())
 
 
+def _vec(v):
+    """Three numbers in any form the Functions take (sequence, array, tensor, iterator) as a tuple of floats."""
+    return tuple(float(x) for x in v)
+
+
 class RenderFn(torch.autograd.Function):
     """(density [nx,ny,nz,cs], colour) -> (rgb [R,3], T_final [R], dist [R]).
 
@@ -87,13 +92,14 @@ class RenderFn(torch.autograd.Function):
 
 
 def render(density, colour, batch, box, *, grid_color, act_shift, halt_T=0.0, bg=(1.0, 1.0, 1.0), want_dist=True):
-    if _eager(density, colour):
+    box, bg = (_vec(box[0]), _vec(box[1])), _vec(bg)
+    if _eager(density, colour) and len(box[0]) == len(box[1]) == len(bg) == 3:
         # None where the call is not one for the kernels: the Function then says why
         out = _native().render(density, colour, batch.ray_offsets, batch.xyz, batch.delta, batch.s_mid, batch.s_len,
-                               batch.n_rays, batch.n_samples, box[0], box[1], grid_color, act_shift, halt_T, bg, want_dist)
+                               batch.n_rays, batch.n_samples, *box, bool(grid_color), act_shift, halt_T, bg, bool(want_dist))
         if out is not None:
             return tuple(out)
-    return RenderFn.apply(density, colour, batch, box, grid_color, act_shift, halt_T, tuple(bg), want_dist)
+    return RenderFn.apply(density, colour, batch, box, grid_color, act_shift, halt_T, bg, want_dist)
 
 
 class DistortionFn(torch.autograd.Function):
@@ -141,8 +147,9 @@ class GatherFn(torch.autograd.Function):
 
 
 def gather(grid, xyz, box):
-    if _eager(grid, xyz):
-        out = _native().gather(grid, xyz, box[0], box[1])
+    box = _vec(box[0]), _vec(box[1])
+    if _eager(grid, xyz) and len(box[0]) == len(box[1]) == 3:
+        out = _native().gather(grid, xyz, *box)
         if out is not None:
             return out
     return GatherFn.apply(grid, xyz, box)

@@ -94,3 +94,39 @@ def test_library_errors_of_a_backward_are_dvgo_errors():
         finally:
             ops.set_debug(before)
     assert errors[0] == errors[1] and _lib.ERRORS[errors[0][0]] == "ERR_UNSORTED"
+
+
+FORMS = {
+    "list": list, "ints": lambda v: [int(x) if x == int(x) else x for x in v], "array": lambda v: __import__("numpy").array(v),
+    "tensor": torch.tensor, "device tensor": lambda v: torch.tensor(v).cuda(), "iterator": iter, "text": lambda v: [str(x) for x in v],
+    "two": lambda v: v[:2], "four": lambda v: [*v, 1.0], "none": lambda v: None,
+}
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_box_and_background_forms(form):
+    # every form the Functions take gives what a tuple gives; the others raise the same error
+    import synth
+    from paper_2206_05085_amd import autograd as mod, ops
+    wl = synth.config2(R=40, N=48, n=24)
+    smp, f = wl.samples, FORMS[form]
+    b = ops.SampleBatch.from_arrays(smp.ray_offsets, smp.xyz, smp.delta, smp.s_mid, smp.s_len)
+    d, c = torch.as_tensor(wl.density.data).cuda(), torch.rand(smp.n_samples, 3, device="cuda")
+    bg, lo, hi = (0.25, 0.5, 1.0), (-1.0, -1.0, -1.0), (1.0, 1.0, 1.0)
+    args = (False, -4.0, 0.0)
+
+    def same(node, function, plain):
+        x, y = _outcome(node), _outcome(function)
+        if isinstance(y, tuple) and isinstance(y[0], type):
+            assert form in ("two", "four", "none") and x == y
+        else:
+            assert torch.equal(_first(x), _first(y)) and torch.equal(_first(x), _first(plain()))
+
+    same(lambda: mod.render(d, c, b, (lo, hi), grid_color=False, act_shift=-4.0, bg=f(bg)),
+         lambda: mod.RenderFn.apply(d, c, b, (lo, hi), *args, tuple(f(bg)), True),
+         lambda: mod.render(d, c, b, (lo, hi), grid_color=False, act_shift=-4.0, bg=bg))
+    same(lambda: mod.render(d, c, b, (f(lo), f(hi)), grid_color=False, act_shift=-4.0),
+         lambda: mod.RenderFn.apply(d, c, b, (f(lo), f(hi)), *args, (1.0, 1.0, 1.0), True),
+         lambda: mod.render(d, c, b, (lo, hi), grid_color=False, act_shift=-4.0))
+    same(lambda: mod.gather(d, b.xyz, (f(lo), f(hi))), lambda: mod.GatherFn.apply(d, b.xyz, (f(lo), f(hi))),
+         lambda: mod.gather(d, b.xyz, (lo, hi)))
