@@ -12,6 +12,8 @@ Functions, 40 us of it on the GPU).
 """
 from __future__ import annotations
 
+import warnings
+
 import torch
 from torch.autograd import forward_ad
 
@@ -22,18 +24,20 @@ _nodes = None
 
 
 def _native():
-    """The extension; raises if it has not been built (the build makes it after libdvgo.so)."""
+    """The extension, or None where it is not built (the Functions serve every call then, warned of once);
+    raises if libdvgo.so itself has not been built."""
     global _nodes
     if _nodes is None:
         from . import _lib
         _lib.lib()
         try:
             from . import _dvgo_autograd
+            _nodes = _dvgo_autograd
         except ImportError as e:
-            raise RuntimeError("the autograd extension is not built: run `python -m paper_2206_05085_amd.build` "
-                               "(or __graft_entry__.build()) first") from e
-        _nodes = _dvgo_autograd
-    return _nodes
+            _nodes = False
+            warnings.warn("the C++ autograd nodes are not built (python -m paper_2206_05085_amd.build); the same kernels "
+                          f"run through the Python Functions, with more host time per call: {e}", RuntimeWarning, stacklevel=3)
+    return _nodes or None
 
 
 def _eager(*tensors) -> bool:
@@ -93,9 +97,9 @@ class RenderFn(torch.autograd.Function):
 
 def render(density, colour, batch, box, *, grid_color, act_shift, halt_T=0.0, bg=(1.0, 1.0, 1.0), want_dist=True):
     box, bg = (_vec(box[0]), _vec(box[1])), _vec(bg)
-    if _eager(density, colour) and len(box[0]) == len(box[1]) == len(bg) == 3:
+    if _eager(density, colour) and len(box[0]) == len(box[1]) == len(bg) == 3 and (native := _native()):
         # None where the call is not one for the kernels: the Function then says why
-        out = _native().render(density, colour, batch.ray_offsets, batch.xyz, batch.delta, batch.s_mid, batch.s_len,
+        out = native.render(density, colour, batch.ray_offsets, batch.xyz, batch.delta, batch.s_mid, batch.s_len,
                                batch.n_rays, batch.n_samples, *box, bool(grid_color), act_shift, halt_T, bg, bool(want_dist))
         if out is not None:
             return tuple(out)
@@ -119,8 +123,8 @@ class DistortionFn(torch.autograd.Function):
 
 
 def distortion(w, ray_offsets, s_mid, s_len):
-    if _eager(w, ray_offsets, s_mid, s_len):
-        loss = _native().distortion(w, ray_offsets, s_mid, s_len)
+    if _eager(w, ray_offsets, s_mid, s_len) and (native := _native()):
+        loss = native.distortion(w, ray_offsets, s_mid, s_len)
         if loss is not None:
             return loss
     return DistortionFn.apply(w, ray_offsets, s_mid, s_len)
@@ -148,8 +152,8 @@ class GatherFn(torch.autograd.Function):
 
 def gather(grid, xyz, box):
     box = _vec(box[0]), _vec(box[1])
-    if _eager(grid, xyz) and len(box[0]) == len(box[1]) == 3:
-        out = _native().gather(grid, xyz, *box)
+    if _eager(grid, xyz) and len(box[0]) == len(box[1]) == 3 and (native := _native()):
+        out = native.gather(grid, xyz, *box)
         if out is not None:
             return out
     return GatherFn.apply(grid, xyz, box)
@@ -177,8 +181,8 @@ class ColorMLPFn(torch.autograd.Function):
 
 
 def color_mlp(feat, W, b, ray_offsets, dirs, n_freq=4):
-    if _eager(feat, *W, *b, ray_offsets, dirs):
-        rgb = _native().color_mlp(feat, W[:3], b[:3], ray_offsets, dirs, n_freq)
+    if _eager(feat, *W, *b, ray_offsets, dirs) and (native := _native()):
+        rgb = native.color_mlp(feat, W[:3], b[:3], ray_offsets, dirs, n_freq)
         if rgb is not None:
             return rgb
     return ColorMLPFn.apply(feat, W[0], b[0], W[1], b[1], W[2], b[2], ray_offsets, dirs, n_freq)

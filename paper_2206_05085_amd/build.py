@@ -55,7 +55,15 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
-    build_autograd(verbose)
+    try:
+        build_autograd(verbose)
+    except (subprocess.CalledProcessError, OSError) as e:
+        # no host C++ compiler, or one that does not take this libtorch's headers: the package works without
+        # the nodes, and an older build of them does not belong to this library
+        if os.path.exists(NATIVE):
+            os.remove(NATIVE)
+        print(f"warning: the C++ autograd nodes were not built ({e}); the Python Functions take their place",
+              file=sys.stderr, flush=True)
     return LIB
 
 
