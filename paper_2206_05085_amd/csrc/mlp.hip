@@ -198,7 +198,8 @@ struct MlpArgs {
     float *rgb;
     unsigned char *img;  // weight image (workspace)
     float *pe;           // [R][PEW] view encodings (workspace)
-    float *rb;           // [R][RBW] layer-1 biases of the rays, b1 + W1 (view encoding), and their largest magnitude
+    float *rb;           // [R][RBW] layer-1 biases of the rays, b1 + W1 (view encoding), and their largest magnitude;
+                         // NULL where the batch has none (ray_rows)
     int *tile_ray;       // [ceil(S/32)] ray of the first sample of each 32-sample tile (workspace)
     int n_tiles;         // ceil(S/32)
     const float *grad_rgb;
@@ -288,9 +289,27 @@ constexpr int PREP_FIXED_BLOCKS = PREP_W2_BLOCKS + PREP_W1_BLOCKS + 1;
 // blocks [0, 16): W2 and W2^T planes; every one of them also reduces max|W2| and the column
 // sums of |W2| from the same loads (block 0 stores sw2 and n2t).  Blocks [16, 20): W1 planes,
 // max|W1| and the row sums of |W1| (block 16 stores sw1, n1, b1max and writes W1F, b1, b3).
-// Block 20: W3, b2, n3t.  Then the rays (PREP_RAYS per block: view encodings, one entry per thread, and
-// the layer-1 biases that follow from them, one unit per thread) and the tile start rays.
+// Block 20: W3, b2, n3t.  Then the rays and the tile start rays.  Where the batch has bias rows (ray_rows) a
+// block takes PREP_RAYS rays: view encodings, one entry per thread, and the layer-1 biases that follow from
+// them, one unit per thread; otherwise PREP_THREADS entries of the encodings, one per thread.
 constexpr int PREP_RAYS = 16;
+
+// blocks of the preparation that serve the rays
+__host__ __device__ __forceinline__ int ray_blocks(const MlpArgs &a) {
+    return a.rb ? (a.n_rays + PREP_RAYS - 1) / PREP_RAYS
+                : (int)(((int64_t)a.n_rays * PEW + PREP_THREADS - 1) / PREP_THREADS);
+}
+
+// entry e of the view encoding of ray r (0 past its 3 + 6 F entries)
+__device__ __forceinline__ float encoding(const MlpArgs &a, int r, int e) {
+    const int F = a.n_freq;
+    if (e >= 3 + 6 * F) return 0.f;
+    const int q = e < 3 ? e : (e - 3) % (3 * F), ax = e < 3 ? e : q % 3;
+    const float d = a.dirs[3 * (int64_t)r + ax];
+    const float t = ldexpf(d, e < 3 ? 0 : q / 3);
+    return e < 3 ? d : (e < 3 + 3 * F ? sinf(t) : cosf(t));
+}
+
 __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
     __shared__ float red[PREP_THREADS / 64];
     __shared__ float sums[PREP_THREADS];
@@ -299,7 +318,7 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
     unsigned char *img = a.img;
     Meta *meta = reinterpret_cast<Meta *>(img + IMG_META);
     const int tid = threadIdx.x, b = blockIdx.x;
-    const int pe_blocks = (a.n_rays + PREP_RAYS - 1) / PREP_RAYS;
+    const int pe_blocks = ray_blocks(a);
     if (b < PREP_W2_BLOCKS) {
         // element i = tid + 512 k sits in column tid % 128 (512 is a multiple of H)
         float m = 0.f, cs = 0.f;
@@ -386,8 +405,12 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
     } else if (b >= PREP_FIXED_BLOCKS + pe_blocks) {
         const int t = (b - PREP_FIXED_BLOCKS - pe_blocks) * PREP_THREADS + tid;
         if (t < a.n_tiles) a.tile_ray[t] = find_ray(a.offs, a.n_rays, TILE * t);
+    } else if (!a.rb) {
+        const int64_t i = (int64_t)(b - PREP_FIXED_BLOCKS) * PREP_THREADS + tid;
+        const int r = (int)(i / PEW);
+        if (r < a.n_rays) a.pe[i] = encoding(a, r, (int)(i - (int64_t)r * PEW));
     } else {
-        const int r0 = (b - PREP_FIXED_BLOCKS) * PREP_RAYS, nr = min(PREP_RAYS, a.n_rays - r0), F = a.n_freq;
+        const int r0 = (b - PREP_FIXED_BLOCKS) * PREP_RAYS, nr = min(PREP_RAYS, a.n_rays - r0);
         float wl[10];  // W1, read with coalesced loads before the encodings are formed
 #pragma unroll
         for (int i = 0; i < 10; ++i) {
@@ -396,13 +419,7 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
         }
         for (int i = tid; i < PREP_RAYS * PEW; i += PREP_THREADS) {
             const int r = i / PEW, e = i - r * PEW;
-            float v = 0.f;
-            if (r < nr && e < 3 + 6 * F) {
-                const int q = e < 3 ? e : (e - 3) % (3 * F), ax = e < 3 ? e : q % 3;
-                const float d = a.dirs[3 * (r0 + r) + ax];
-                const float t = ldexpf(d, e < 3 ? 0 : q / 3);
-                v = e < 3 ? d : (e < 3 + 3 * F ? sinf(t) : cosf(t));
-            }
+            const float v = r < nr ? encoding(a, r0 + r, e) : 0.f;
             enc[r][e] = v;
             if (r < nr) a.pe[(int64_t)r0 * PEW + i] = v;
         }
@@ -410,7 +427,7 @@ __global__ __launch_bounds__(PREP_THREADS) void mlp_prep_kernel(MlpArgs a) {
         for (int i = 0; i < 10; ++i)
             if (tid + i * PREP_THREADS < H * 39) w1[tid + i * PREP_THREADS] = wl[i];
         __syncthreads();
-        const int u = tid & (H - 1), NE = 3 + 6 * F;
+        const int u = tid & (H - 1), NE = 3 + 6 * a.n_freq;
         const float *w = w1 + u * a.n_in + a.in_feat;
         const float bu = a.b1[u];
         float acc[PREP_RAYS * H / PREP_THREADS];
@@ -492,10 +509,10 @@ __device__ __forceinline__ void copy_to_lds(unsigned char *dst, const unsigned c
 // reads the lane's 8 operand slots (hf, e) as logical index 16 ks + 8 (e / 4) + 4 hf + e % 4, so a row
 // tile of one layer's output is two K-steps of the next layer's B operand without any data movement.  W1
 // and W2 sit in LDS (both parts), their columns in that slot order; three waves per SIMD (12 per block,
-// at most 168 registers).  In the split mode layer 1 multiplies the features only (one K-step): the view
-// encoding is the same for all samples of a ray, and its part of layer 1 is the ray's bias row, made once
-// per ray by the preparation.  (The FP16 mode keeps the encoding in the product, K = 48: its operands are
-// rounded, and so is its encoding.)
+// at most 168 registers).  With ROWS (split mode, batches that have bias rows) layer 1 multiplies the features
+// only (one K-step): the view encoding is the same for all samples of a ray, and its part of layer 1 is the
+// ray's bias row, made once per ray by the preparation.  Otherwise the encoding stays in the product, K = 48.
+// (So it does in the FP16 mode: its operands are rounded, and so is its encoding.)
 //
 // Bound by the matrix and vector units together, which overlap by about half on this chip (measured: eight
 // 32 x 32 x 16 products and 56 FMAs of two waves take 188 ns where the products alone take 145 and the FMAs
@@ -509,10 +526,10 @@ constexpr int FWD_WAVES = 12, FWD_THREADS = 64 * FWD_WAVES;
 
 // LDS row strides: a 16-byte read of 32 rows at one column runs without bank conflicts when the stride is
 // an odd multiple of 16 bytes.
-template <bool SPLIT>
+template <bool SPLIT, bool ROWS>
 struct FwdLds {
-    static constexpr int K1 = SPLIT ? 1 : 3;         // K-steps of layer 1
-    static constexpr int RS1 = SPLIT ? 24 : 56;      // halves per W1 row
+    static constexpr int K1 = ROWS ? 1 : 3;          // K-steps of layer 1
+    static constexpr int RS1 = ROWS ? 24 : 56;       // halves per W1 row
     static constexpr int W2H = 0, W2L = W2H + H * FRS2 * 2, W1H = W2L + (SPLIT ? H * FRS2 * 2 : 0),
                          W1L = W1H + H * RS1 * 2,
                          SMALL = W1L + (SPLIT ? H * RS1 * 2 : 0),  // b1, b2, W3, b3, meta, laid out as in the image
@@ -560,9 +577,10 @@ __device__ __forceinline__ int ray_in_tile(const int *offs, int R, int r0, int w
     return ray;
 }
 
-template <bool SPLIT, int GM>
+template <bool SPLIT, int GM, bool ROWS>
 __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
-    using L = FwdLds<SPLIT>;
+    static_assert(SPLIT || !ROWS, "the FP16 mode rounds the encoding");
+    using L = FwdLds<SPLIT, ROWS>;
     constexpr int K1 = L::K1, FRS1 = L::RS1;
     __shared__ __attribute__((aligned(16))) unsigned char sm[L::END];
     copy_rows_to_lds<32>(sm + L::W2H, FRS2 * 2, a.img + IMG_W2H, RS2 * 2);
@@ -623,16 +641,16 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
         const int sc = sv ? s : a.S - 1;
         const int ray = min(ray_in_tile(a.offs, a.n_rays, r0, win, wt * TILE, s), a.n_rays - 1);
         // This lane's inputs, slot groups (ks, i) = columns 16 ks + 8 i + 4 hf ..: features 4 hf .. and
-        // (hf = 0) 8 .. 11, view encoding 0..3 (hf = 1; FP16 mode), then encoding 4 + 4 hf, 12 + 4 hf,
-        // 20 + 4 hf, 28 + 4 hf (FP16 mode).  Split mode: the ray's bias row instead of the encoding.
-        float4 in[2 * K1], rb[SPLIT ? 16 : 1];
+        // (hf = 0) 8 .. 11, view encoding 0..3 (hf = 1), then encoding 4 + 4 hf, 12 + 4 hf, 20 + 4 hf,
+        // 28 + 4 hf.  ROWS: the ray's bias row instead of the encoding.
+        float4 in[2 * K1], rb[ROWS ? 16 : 1];
         float rbmax = 0.f;
         const float *pe = a.pe + (int64_t)ray * PEW + 4 * hf;
-        if (SPLIT) {
+        if (ROWS) {
             const float *row = a.rb + (int64_t)ray * RBW;
             rbmax = row[H];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) rb[SPLIT ? i : 0] = *reinterpret_cast<const float4 *>(row + 8 * i + 4 * hf);
+            for (int i = 0; i < 16; ++i) rb[ROWS ? i : 0] = *reinterpret_cast<const float4 *>(row + 8 * i + 4 * hf);
         } else {
 #pragma unroll
             for (int i = 2; i < 2 * K1; ++i) in[i] = *reinterpret_cast<const float4 *>(pe + 8 * i - 12);
@@ -659,7 +677,7 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
         }
         if (!f0) in[0] = none;
         if (!f1) in[1] = none;
-        if (!SPLIT && hf) in[1] = *reinterpret_cast<const float4 *>(pe - 4);
+        if (!ROWS && hf) in[1] = *reinterpret_cast<const float4 *>(pe - 4);
         // the next tile's first ray and window entry (the scalar load of the one after goes ahead)
         r0 = r0n;
         r0n = first_ray(wt + 2 * wstep);
@@ -674,7 +692,7 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
                 m = fmaxf(m, fmaxf(fmaxf(fabsf(in[g].x), fabsf(in[g].y)), fmaxf(fabsf(in[g].z), fabsf(in[g].w))));
             }
             m = fmaxf(m, other_half(m));
-            const int ex = scale_exp(m), e1 = scale_exp(SPLIT ? meta.n1f * m + rbmax : meta.n1 * m + meta.b1max);
+            const int ex = scale_exp(m), e1 = scale_exp(ROWS ? meta.n1f * m + rbmax : meta.n1 * m + meta.b1max);
             const float sx = pow2(ex);
 #pragma unroll
             for (int ks = 0; ks < K1; ++ks) {
@@ -715,7 +733,7 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
         // piece i of the end of layer 1's row tile m: half i % 2 of h1's K-step 2 m + i / 2
         h4 hh[16], hl[16];
         auto end1 = [&](int m, int i, const v16f &c) {
-            const float4 bb = SPLIT ? rb[SPLIT ? 4 * m + i : 0] : *reinterpret_cast<const float4 *>(b1 + 32 * m + 8 * i);
+            const float4 bb = ROWS ? rb[ROWS ? 4 * m + i : 0] : *reinterpret_cast<const float4 *>(b1 + 32 * m + 8 * i);
             const int r = 4 * i;
             const float v[4] = {fmaxf(fmaf(c[r], un1, bb.x), 0.f), fmaxf(fmaf(c[r + 1], un1, bb.y), 0.f),
                                 fmaxf(fmaf(c[r + 2], un1, bb.z), 0.f), fmaxf(fmaf(c[r + 3], un1, bb.w), 0.f)};
@@ -1656,13 +1674,20 @@ int bwd_blocks(int64_t S) {
     return (int)(t < MAX_BLOCKS ? (t < 1 ? 1 : t) : MAX_BLOCKS);
 }
 
+// Whether the preparation makes the rays' bias rows, which the split forward then reads: a rule on the batch
+// alone, since one preparation serves every call on it.  A row costs its ray 128 x 39 FMAs and 528 bytes, and
+// saves two of layer 1's three K-steps on each of the ray's samples.  300,000 samples, preparation and forward
+// without rows and with them, us: 6 samples a ray 51 and 64, 12 49 and 53, 20 48.5 and 47.6, 40 47 and 44, 100
+// 47 and 43.  Up to a few thousand rays the row blocks run beside those of the weights (0.7 us at 7,500).
+bool ray_rows(int32_t R, int64_t S) { return R <= 8192 || S >= 24 * (int64_t)R; }
+
 size_t ws_layout(const dvgo_color_mlp *m, int32_t R, int64_t S, size_t *off_pe, size_t *off_rb, size_t *off_tr,
                  size_t *off_part) {
     size_t o = align_up((size_t)IMG_BYTES, 256);
     *off_pe = o;
     o += align_up((size_t)R * PEW * 4, 256);
     *off_rb = o;
-    o += align_up((size_t)R * RBW * 4, 256);
+    if (ray_rows(R, S)) o += align_up((size_t)R * RBW * 4, 256);
     *off_tr = o;
     o += align_up((size_t)((S + TILE - 1) / TILE) * 4, 256);
     *off_part = o;
@@ -1697,7 +1722,7 @@ int setup(const dvgo_color_mlp *m, int32_t R, const int32_t *offs, const float *
     a.feat_vec = m->in_feat == 12 && ((uintptr_t)feat & 15) == 0;
     a.img = (unsigned char *)ws;
     a.pe = (float *)((char *)ws + off_pe);
-    a.rb = (float *)((char *)ws + off_rb);
+    a.rb = ray_rows(R, S) ? (float *)((char *)ws + off_rb) : nullptr;
     a.tile_ray = (int *)((char *)ws + off_tr);
     a.n_tiles = (int)((S + TILE - 1) / TILE);
     a.partial = (float *)((char *)ws + off_part);
@@ -1709,15 +1734,16 @@ template <int GM>
 int launch_fwd(const MlpArgs &a, const dvgo_color_mlp *m, hipStream_t st) {
     const dim3 grid(a.n_tiles < MAX_BLOCKS ? a.n_tiles : MAX_BLOCKS);
     if (m->precision == DVGO_MLP_F16)
-        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM>), grid, dim3(FWD_THREADS), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM, false>), grid, dim3(FWD_THREADS), 0, st, a);
+    else if (a.rb)
+        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, true>), grid, dim3(FWD_THREADS), 0, st, a);
     else
-        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM>), grid, dim3(FWD_THREADS), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, false>), grid, dim3(FWD_THREADS), 0, st, a);
     return check_hip(hipGetLastError(), "mlp_fwd_kernel launch");
 }
 
 int launch_prep(const MlpArgs &a, hipStream_t st) {
-    const int n = PREP_FIXED_BLOCKS + (a.n_rays + PREP_RAYS - 1) / PREP_RAYS +
-                  (a.n_tiles + PREP_THREADS - 1) / PREP_THREADS;
+    const int n = PREP_FIXED_BLOCKS + ray_blocks(a) + (a.n_tiles + PREP_THREADS - 1) / PREP_THREADS;
     hipLaunchKernelGGL(mlp_prep_kernel, dim3(n), dim3(PREP_THREADS), 0, st, a);
     return check_hip(hipGetLastError(), "mlp_prep_kernel launch");
 }
