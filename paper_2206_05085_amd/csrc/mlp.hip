@@ -522,7 +522,8 @@ __device__ __forceinline__ void copy_to_lds(unsigned char *dst, const unsigned c
 // 143 -> 124, the rays' bias rows and the ray search by ray starts (instead of six dependent lane
 // shuffles) 124 -> 108.
 constexpr int FRS2 = 136;  // halves per W2 row in the forward's LDS (128 used)
-constexpr int FWD_WAVES = 12, FWD_THREADS = 64 * FWD_WAVES;
+template <bool SPLIT>
+constexpr int FWD_WAVES = SPLIT ? 12 : 16;
 
 // LDS row strides: a 16-byte read of 32 rows at one column runs without bank conflicts when the stride is
 // an odd multiple of 16 bytes.
@@ -550,7 +551,7 @@ __device__ __forceinline__ v16f mfma32(h8 a, h8 b, v16f c) {
 template <int GROUPS>
 __device__ __forceinline__ void copy_rows_to_lds(unsigned char *dst, int dstride, const unsigned char *src,
                                                  int sstride) {
-    for (int i = threadIdx.x; i < H * GROUPS; i += FWD_THREADS) {
+    for (int i = threadIdx.x; i < H * GROUPS; i += (int)blockDim.x) {
         const int r = i / GROUPS, u = i - r * GROUPS;
         const int from = 8 * (u >> 3) + 2 * (u & 3) + ((u >> 2) & 1), to = 4 * (u >> 2) + 2 * (u & 1) + ((u >> 1) & 1);
         *reinterpret_cast<uint2 *>(dst + r * dstride + 8 * to) =
@@ -577,8 +578,29 @@ __device__ __forceinline__ int ray_in_tile(const int *offs, int R, int r0, int w
     return ray;
 }
 
+// Channels c0 .. c0 + 3 and c1 .. c1 + 3 of a lookup, the bits of interp4 for each.  A corner's two loads
+// follow each other: they mostly touch the same line, which the L1 does not keep until a second pass where the
+// points are scattered (244,000 random points, both modes, eight loads of one part and then of the other: 51.8
+// and 45.1 us; this way 45.5 and 41.1).
+__device__ __forceinline__ void interp4_pair(const DevGrid &g, const Tri &t, int c0, int c1, float4 &a, float4 &b) {
+    const auto fma4 = [](float4 &acc, float w, const float4 &v) {
+        acc.x = __builtin_fmaf(w, v.x, acc.x);
+        acc.y = __builtin_fmaf(w, v.y, acc.y);
+        acc.z = __builtin_fmaf(w, v.z, acc.z);
+        acc.w = __builtin_fmaf(w, v.w, acc.w);
+    };
+    a = b = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const float *p = g.data + t.base + corner_off(g, c);
+        const float4 u = *reinterpret_cast<const float4 *>(p + c0), v = *reinterpret_cast<const float4 *>(p + c1);
+        fma4(a, t.w[c], u);
+        fma4(b, t.w[c], v);
+    }
+}
+
 template <bool SPLIT, int GM, bool ROWS>
-__global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
+__global__ __launch_bounds__(64 * FWD_WAVES<SPLIT>) void mlp_fwd_kernel(MlpArgs a) {
     static_assert(SPLIT || !ROWS, "the FP16 mode rounds the encoding");
     using L = FwdLds<SPLIT, ROWS>;
     constexpr int K1 = L::K1, FRS1 = L::RS1;
@@ -605,7 +627,7 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
     const int nwt = a.n_tiles;
     // neighbouring tiles go to neighbouring blocks: a small batch spreads over the CUs
     const int wt0 = blockIdx.x + (int)gridDim.x * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wstep = gridDim.x * FWD_WAVES;
+    const int wstep = gridDim.x * FWD_WAVES<SPLIT>;
     if (wt0 >= nwt) return;
     // First ray of a tile (past the last tile, the last tile's ray), read through the scalar cache: the
     // index is wave-uniform and the table is read-only here.
@@ -646,25 +668,34 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
         float4 in[2 * K1], rb[ROWS ? 16 : 1];
         float rbmax = 0.f;
         const float *pe = a.pe + (int64_t)ray * PEW + 4 * hf;
-        if (ROWS) {
+        auto bias_row = [&]() {
             const float *row = a.rb + (int64_t)ray * RBW;
             rbmax = row[H];
 #pragma unroll
             for (int i = 0; i < 16; ++i) rb[ROWS ? i : 0] = *reinterpret_cast<const float4 *>(row + 8 * i + 4 * hf);
-        } else {
+        };
+        if (ROWS && !GM) bias_row();
+        if (!ROWS) {
 #pragma unroll
             for (int i = 2; i < 2 * K1; ++i) in[i] = *reinterpret_cast<const float4 *>(pe + 8 * i - 12);
         }
         store_out();  // the previous tile's output
         if (GM) {
             const Tri t = trilinear<GM == 2>(a.fg, pt[0], pt[1], pt[2]);
-            in[0] = interp4(a.fg, t, f0 ? 4 * hf : 0);
-            in[1] = none;
-            if (hf == 0) in[1] = interp4(a.fg, t, f1 ? 8 : 0);
+            in[0] = in[1] = none;
+            if (a.in_feat > 8) {
+                interp4_pair(a.fg, t, 4 * hf, 8, in[0], in[1]);
+            } else {
+                in[0] = interp4(a.fg, t, f0 ? 4 * hf : 0);
+            }
             if (a.feat_out && sv) {
                 float *fo = a.feat_out + (int64_t)s * a.in_feat;
                 if (f0) *reinterpret_cast<float4 *>(fo + 4 * hf) = in[0];
                 if (f1) *reinterpret_cast<float4 *>(fo + 8) = in[1];
+            }
+            if (ROWS) {  // after the corner rows: both at once do not fit the registers
+                __builtin_amdgcn_sched_barrier(0);
+                bias_row();
             }
             points(wt + wstep);
         } else if (a.feat_vec) {
@@ -1734,11 +1765,11 @@ template <int GM>
 int launch_fwd(const MlpArgs &a, const dvgo_color_mlp *m, hipStream_t st) {
     const dim3 grid(a.n_tiles < MAX_BLOCKS ? a.n_tiles : MAX_BLOCKS);
     if (m->precision == DVGO_MLP_F16)
-        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM, false>), grid, dim3(FWD_THREADS), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM, false>), grid, dim3(64 * FWD_WAVES<false>), 0, st, a);
     else if (a.rb)
-        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, true>), grid, dim3(FWD_THREADS), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, true>), grid, dim3(64 * FWD_WAVES<true>), 0, st, a);
     else
-        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, false>), grid, dim3(FWD_THREADS), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, false>), grid, dim3(64 * FWD_WAVES<true>), 0, st, a);
     return check_hip(hipGetLastError(), "mlp_fwd_kernel launch");
 }
 
