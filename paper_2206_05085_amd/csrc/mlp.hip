@@ -563,13 +563,25 @@ __device__ __forceinline__ void copy_rows_to_lds(unsigned char *dst, int dstride
 __device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32, 64); }
 
 // The ray of sample s of the 32-sample tile whose first sample lies on ray r0, where lane l holds w =
-// offs[min(r0 + l, R)]: only rays with samples matter, and those that start inside the tile are few, so
-// they are taken one by one (wave-uniform).  All 64 lanes must call it.
+// offs[min(r0 + l, R)]: only rays with samples matter, and those that start inside the tile are mostly few, so
+// they are taken one by one (wave-uniform); more than 8 by a binary search over the window, six dependent lane
+// shuffles.  All 64 lanes must call it.
 __device__ __forceinline__ int ray_in_tile(const int *offs, int R, int r0, int w, int tile0, int s) {
     const int after = __shfl_down(w, 1, 64);
     const bool starts = lane() < 63 && w > tile0 && w < tile0 + TILE && after > w;
     int ray = r0;
-    for (unsigned long long b = __ballot(starts); b; b &= b - 1) {
+    unsigned long long b = __ballot(starts);
+    if (__popcll(b) > 8) {
+        int at = 0;  // the last window entry at or before s
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            const int v = __shfl(w, at + d, 64);
+            if (v <= s) at += d;
+        }
+        ray = r0 + at;
+        b = 0;
+    }
+    for (; b; b &= b - 1) {
         const int l = __ffsll((long long)b) - 1;
         if (s >= __builtin_amdgcn_readlane(w, l)) ray = r0 + l;
     }
