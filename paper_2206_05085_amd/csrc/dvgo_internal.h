@@ -282,6 +282,38 @@ struct SlotWalk {
             }
         }
     }
+    // group g (a multiple of 2 K) takes over the sums of group g + K on the vertices both hold; whether any did (wave-uniform)
+    template <int K>
+    __device__ __forceinline__ bool join_at() {
+        const int r = group & (2 * K - 1);
+        const bool take = r == 0 && group + K < NG, give = r == K && group < NG;
+        const int other = lane() + (take ? K * GL : (give ? -K * GL : 0));
+        bool same[SL], any = false;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const int at = __shfl(cur[s], other, 64);
+            same[s] = (take || give) && at == cur[s];
+            any |= same[s] && acc[s] != 0.f;
+        }
+        if (!__any(any)) return false;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+            const float v = __shfl(acc[s], other, 64);
+            acc[s] = same[s] ? (take ? acc[s] + v : 0.f) : acc[s];
+        }
+        return true;
+    }
+    // Groups of the wave that end on the same vertices join their sums: neighbours first, then, if any two of
+    // them agreed, groups two and four apart.  Costs a wave on ordinary rays one look (no difference measured);
+    // where a wave's samples all lie in one cell (rays behind the box's face, a small grid) its groups would
+    // otherwise each send the same eight vertices: render_bwd of 491,520 samples at one point 786 -> 111 us,
+    // of 300,000 samples along rays through an 8^3 grid 123 -> 67.  All 64 lanes must call it.
+    __device__ __forceinline__ void join() {
+        static_assert(NG <= 8, "three distances");
+        if (!join_at<1>()) return;
+        if constexpr (NG > 2) join_at<2>();
+        if constexpr (NG > 4) join_at<4>();
+    }
     template <class Sum>
     __device__ __forceinline__ void finish(const Sum &sum) {
 #pragma unroll
@@ -309,6 +341,7 @@ __device__ __forceinline__ void walk_chunk(const DevGrid &g, int n, const Cell &
     const float fc = wk.ch == 0 ? f0 : (wk.ch == 1 ? f1 : f2);
     const GlobalSum sum{g.grad + wk.ch};
     for (int t = 0; t < cnt; ++t) wk.step(g.sx, g.sy, g.cs, rec[b + t], vals[b + t] * fc, sum);
+    wk.join();
     wk.finish(sum);
     lds_fence();
 }

@@ -204,6 +204,7 @@ __global__ __launch_bounds__(kBlock) void scatter_kernel(DevGrid g, int64_t S, c
         for (int t = 0; t < cnt; ++t) wk.step(g.sx, g.sy, g.cs, rp[t], vp[t * g.C], sum);
         lds_fence();
     }
+    wk.join();
     wk.finish(sum);
 }
 
