@@ -802,13 +802,18 @@ __global__ __launch_bounds__(256) void bin_place_kernel(int64_t S, const int2 *_
     }
 }
 
-// One channel, a block per brick.  A brick of at most 64 samples takes the first wave, a sample a lane,
-// straight to global atomics; a larger one the whole block: an LDS tile of BV^3 vertices, flushed with one
-// global atomic per touched vertex, each thread walking a run of the brick's samples (SlotWalk, the eight
-// classes in registers), so that vertices shared along a ray merge before the LDS atomics, which would
-// otherwise collide.  Bound by latency: 981,504 samples in 8,000 bricks 75 -> 57 us; 2,293,760 samples in
-// 64,000 bricks, most of them with a handful and a thousand with 1,500 to 4,300, 219 -> 66 us.
-constexpr int BRICK_THREADS = 256;
+// One channel, a block per brick.  A brick of a few samples takes the first wave, a sample a lane, straight to
+// global atomics; a larger one the whole block: an LDS tile of BV^3 vertices, flushed with one global atomic
+// per touched vertex, each thread walking a run of the brick's samples (SlotWalk, the eight classes in
+// registers), so that vertices shared along a ray merge before the LDS atomics, which would otherwise
+// collide.
+// BRICK_LIGHT: the tile's cost (its clearing, two barriers, the flush's look at every vertex) against eight
+// scattered one-float atomics a sample, where the flush sends rows of neighbouring vertices.  Limits 0, 4, 8,
+// 16, 32 and 64: 307,200 samples along rays in 8,000 bricks (38 a brick) 24.1, 23.9, 23.5, 22.9, 38 and 74 us;
+// 120,000 along short rays (15 a brick) 23.2, 22.8, 20.7, 30.7, 39 and 43; 300,000 scattered ones (37 a brick)
+// 34.1, 34.3, 34.0, 35.3, 41 and 96; 2,300,000 in 64,000 bricks, most with a handful and some with thousands,
+// 229, 226, 230, 287, 359 and 359.
+constexpr int BRICK_THREADS = 256, BRICK_LIGHT = 8;
 
 template <bool W>
 __global__ __launch_bounds__(BRICK_THREADS) void brick_scatter_kernel(DevGrid g, BinGeom bg,
@@ -818,7 +823,7 @@ __global__ __launch_bounds__(BRICK_THREADS) void brick_scatter_kernel(DevGrid g,
                                                                       const int *__restrict__ perm) {
     __shared__ double tile[BV * BV * BV];
     const int b = blockIdx.x, beg = offs[b], end = offs[b + 1];
-    if (end - beg <= 64) {
+    if (end - beg <= BRICK_LIGHT) {
         if ((int)threadIdx.x < end - beg) {
             const int64_t s = perm[beg + threadIdx.x];
             const Cell c = cell_of<W>(g, xyz[3 * s], xyz[3 * s + 1], xyz[3 * s + 2]);
