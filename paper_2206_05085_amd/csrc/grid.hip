@@ -802,11 +802,11 @@ __global__ __launch_bounds__(256) void bin_place_kernel(int64_t S, const int2 *_
     }
 }
 
-// One channel, a block per brick.  A brick of a few samples takes the first wave, a sample a lane, straight to
-// global atomics; a larger one the whole block: an LDS tile of BV^3 vertices, flushed with one global atomic
-// per touched vertex, each thread walking a run of the brick's samples (SlotWalk, the eight classes in
-// registers), so that vertices shared along a ray merge before the LDS atomics, which would otherwise
-// collide.
+// Up to four channels (C <= NC), a block per brick.  A brick of a few samples goes straight to global atomics,
+// a (sample, channel) a thread; a larger one through an LDS tile of BV^3 vertices x NC channels, flushed with one
+// global atomic per touched vertex channel, groups of NC threads walking a run of the brick's samples
+// (SlotWalk, the eight classes in registers), so that vertices shared along a ray merge before the LDS atomics,
+// which would otherwise collide.
 // BRICK_LIGHT: the tile's cost (its clearing, two barriers, the flush's look at every vertex) against eight
 // scattered one-float atomics a sample, where the flush sends rows of neighbouring vertices.  Limits 0, 4, 8,
 // 16, 32 and 64: 307,200 samples along rays in 8,000 bricks (38 a brick) 24.1, 23.9, 23.5, 22.9, 38 and 74 us;
@@ -815,20 +815,22 @@ __global__ __launch_bounds__(256) void bin_place_kernel(int64_t S, const int2 *_
 // 229, 226, 230, 287, 359 and 359.
 constexpr int BRICK_THREADS = 256, BRICK_LIGHT = 8;
 
-template <bool W>
+template <int NC, bool W>
 __global__ __launch_bounds__(BRICK_THREADS) void brick_scatter_kernel(DevGrid g, BinGeom bg,
                                                                       const float *__restrict__ xyz,
                                                                       const float *__restrict__ vals,
                                                                       const int *__restrict__ offs,
                                                                       const int *__restrict__ perm) {
-    __shared__ double tile[BV * BV * BV];
-    const int b = blockIdx.x, beg = offs[b], end = offs[b + 1];
+    __shared__ double tile[BV * BV * BV * NC];
+    static_assert(BRICK_LIGHT * NC <= BRICK_THREADS, "a thread per sample and channel");
+    const int b = blockIdx.x, beg = offs[b], end = offs[b + 1], nc = NC == 1 ? 1 : g.C;
     if (end - beg <= BRICK_LIGHT) {
-        if ((int)threadIdx.x < end - beg) {
-            const int64_t s = perm[beg + threadIdx.x];
+        const int i = threadIdx.x / NC, ch = threadIdx.x - i * NC;
+        if (i < end - beg && ch < nc) {
+            const int64_t s = perm[beg + i];
             const Cell c = cell_of<W>(g, xyz[3 * s], xyz[3 * s + 1], xyz[3 * s + 2]);
-            const float v = vals[s];
-            float *p = g.grad + c.ix * g.sx + c.iy * g.sy + c.iz * g.cs;
+            const float v = vals[s * nc + ch];
+            float *p = g.grad + c.ix * g.sx + c.iy * g.sy + c.iz * g.cs + ch;
             if (v != 0.f) {
 #pragma unroll
                 for (int k = 0; k < 8; ++k)
@@ -839,37 +841,53 @@ __global__ __launch_bounds__(BRICK_THREADS) void brick_scatter_kernel(DevGrid g,
     }
     const int bz = b % bg.nb[2], by = (b / bg.nb[2]) % bg.nb[1], bx = b / (bg.nb[2] * bg.nb[1]);
     const int x0 = bx * BRICK, y0 = by * BRICK, z0 = bz * BRICK;
-    for (int i = threadIdx.x; i < BV * BV * BV; i += BRICK_THREADS) tile[i] = 0.0;
+    for (int i = threadIdx.x; i < BV * BV * BV * NC; i += BRICK_THREADS) tile[i] = 0.0;
     __syncthreads();
-    const int len = (end - beg + BRICK_THREADS - 1) / BRICK_THREADS;
-    const LdsSum sum{tile};
-    SlotWalk<1, 8> wk;
-    const int i0 = beg + (int)threadIdx.x * len, e = min(i0 + len, end);
-    if (i0 < e) {
+    using Walk = SlotWalk<NC, 8>;
+    constexpr int RUNS = BRICK_THREADS / 64 * Walk::NG;
+    const int len = (end - beg + RUNS - 1) / RUNS;
+    Walk wk;
+    const LdsSum sum{tile + wk.ch};
+    const int i0 = beg + ((int)(threadIdx.x >> 6) * Walk::NG + wk.group) * len, e = min(i0 + len, end);
+    const int ch = NC == 1 ? 0 : wk.ch;
+    if (wk.group < Walk::NG && i0 < e && ch < nc) {
         // the next sample's row is loaded, and the index after it, while this one is added
         int64_t s1 = perm[min(i0 + 1, e - 1)];
         const int64_t s0 = perm[i0];
-        float px = xyz[3 * s0], py = xyz[3 * s0 + 1], pz = xyz[3 * s0 + 2], pv = vals[s0];
+        float px = xyz[3 * s0], py = xyz[3 * s0 + 1], pz = xyz[3 * s0 + 2], pv = vals[s0 * nc + ch];
         for (int i = i0; i < e; ++i) {
             const float x = px, y = py, z = pz, v = pv;
             const int64_t s2 = perm[min(i + 2, e - 1)];
-            px = xyz[3 * s1], py = xyz[3 * s1 + 1], pz = xyz[3 * s1 + 2], pv = vals[s1];
+            px = xyz[3 * s1], py = xyz[3 * s1 + 1], pz = xyz[3 * s1 + 2], pv = vals[s1 * nc + ch];
             s1 = s2;
             const Cell c = cell_of<W>(g, x, y, z);
-            wk.step(BV * BV, BV, 1, stage_cell(((c.ix - x0) * BV + (c.iy - y0)) * BV + (c.iz - z0), c), v, sum);
+            const int low = (((c.ix - x0) * BV + (c.iy - y0)) * BV + (c.iz - z0)) * NC;
+            wk.step(BV * BV * NC, BV * NC, NC, stage_cell(low, c), v, sum);
         }
     }
     wk.finish(sum);
     __syncthreads();
     // flush in memory order so consecutive lanes hit consecutive addresses
-    for (int v = threadIdx.x; v < BV * BV * BV; v += BRICK_THREADS) {
-        const float t = (float)tile[v];
+    for (int i = threadIdx.x; i < BV * BV * BV * NC; i += BRICK_THREADS) {
+        const float t = (float)tile[i];
         if (t == 0.f) continue;
+        const int v = i / NC, ch = i - v * NC;
         const int lz = v % BV, ly = (v / BV) % BV, lx = v / (BV * BV);
         const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
         if (gx < g.n[0] && gy < g.n[1] && gz < g.n[2])
-            unsafeAtomicAdd(g.grad + (int64_t)gx * g.sx + (int64_t)gy * g.sy + (int64_t)gz * g.cs, t);
+            unsafeAtomicAdd(g.grad + (int64_t)gx * g.sx + (int64_t)gy * g.sy + (int64_t)gz * g.cs + ch, t);
     }
+}
+
+template <int NC>
+void launch_brick_scatter(const DevGrid &dg, const BinGeom &bg, const float *xyz, const float *vals, const BinWs &w,
+                          hipStream_t st) {
+    if (dg.warp)
+        hipLaunchKernelGGL((brick_scatter_kernel<NC, true>), dim3(bg.n), dim3(BRICK_THREADS), 0, st, dg, bg, xyz, vals,
+                           w.offs, w.perm);
+    else
+        hipLaunchKernelGGL((brick_scatter_kernel<NC, false>), dim3(bg.n), dim3(BRICK_THREADS), 0, st, dg, bg, xyz, vals,
+                           w.offs, w.perm);
 }
 
 int bin_setup(const dvgo_grid *g, int64_t S, const void *ws, size_t ws_bytes, DevGrid &dg, BinGeom &bg, BinWs &w,
@@ -945,14 +963,16 @@ extern "C" int dvgo_grid_scatter_binned(const dvgo_grid *g, int64_t n_samples, c
     if (n_samples == 0) return DVGO_OK;
     if (!xyz || !grad_out) return set_error(DVGO_ERR_NULL, "xyz or grad_out is NULL");
     const hipStream_t st = (hipStream_t)stream;
-    // more than one channel: the slot walk over the samples in their own order (12 channels, 981,504
-    // samples on 160^3: 193 us; the brick tiles took 792 us, their LDS atomics growing with the channels)
-    if (g->channels > 1) return scatter_any(dg, n_samples, xyz, grad_out, st);
-    const dim3 grid(bg.n), block(BRICK_THREADS);
-    if (dg.warp)
-        hipLaunchKernelGGL((brick_scatter_kernel<true>), grid, block, 0, st, dg, bg, xyz, grad_out, w.offs, w.perm);
-    else
-        hipLaunchKernelGGL((brick_scatter_kernel<false>), grid, block, 0, st, dg, bg, xyz, grad_out, w.offs, w.perm);
+    // The bricks serve one channel, and two to four where there are enough of them to fill half the chip; the
+    // rest takes the slot walk over the samples in their own order, as dvgo_grid_scatter does (its merging is
+    // along rays, the tiles' also across them).  Bricks and walk, us: 983,040 samples on 160^3 (8,000 bricks)
+    // along rays 3 channels 66 and 125, 4 channels 74 and 118, 8 channels 137 and 133; in random order 67 and 224,
+    // 76 and 214, 139 and 254; on 48^3 (216 bricks) along rays 41 and 51, 53 and 49; on 32^3 (64 bricks) 48 and
+    // 10, 62 and 11.  (12 channels on 160^3: 793 with a tile in float, 193.)
+    if (dg.C > 4 || (dg.C > 1 && bg.n < 128)) return scatter_any(dg, n_samples, xyz, grad_out, st);
+    if (dg.C == 1) launch_brick_scatter<1>(dg, bg, xyz, grad_out, w, st);
+    else if (dg.C <= 3) launch_brick_scatter<3>(dg, bg, xyz, grad_out, w, st);
+    else launch_brick_scatter<4>(dg, bg, xyz, grad_out, w, st);
     return check_hip(hipGetLastError(), "brick_scatter_kernel launch");
 }
 
