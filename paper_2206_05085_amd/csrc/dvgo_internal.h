@@ -116,9 +116,11 @@ __device__ __forceinline__ void axis_coord(float x, float shi, float slo, float 
 // Cell index and fraction of a point addressed through the unbounded-scene contraction
 // (Eq. 4, p = inf or 2).  The contraction and the index map run in double, so the fraction
 // is accurate to float32 although the contracted point is a derived value; the clamping
-// matches axis_coord.
+// matches axis_coord.  Every rounding is written out (explicit FMAs, no contraction): the binning and the
+// scatter of the bins each form a point's cell, and an LDS tile has room only for cells that agree.
 __device__ __forceinline__ void warped_coords(const DevGrid &g, float x, float y, float z, int (&i)[3],
                                               float (&f)[3]) {
+#pragma clang fp contract(off)
     double p[3] = {(double)x, (double)y, (double)z};
     double n;
     if (g.warp == DVGO_WARP_CONTRACT_INF) {
@@ -126,13 +128,16 @@ __device__ __forceinline__ void warped_coords(const DevGrid &g, float x, float y
         n = fabs(p[1]) > n ? fabs(p[1]) : n;
         n = fabs(p[2]) > n ? fabs(p[2]) : n;
     } else {
-        n = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2]);
+        n = sqrt(__builtin_fma(p[2], p[2], __builtin_fma(p[0], p[0], p[1] * p[1])));
     }
-    const double r = 1.0 / n;  // the one division of the contraction
-    const double s = n > 1.0 ? (1.0 + g.wb - g.wb * r) * r : 1.0;
+    double s = 1.0;
+    if (n > 1.0) {
+        const double r = 1.0 / n;
+        s = __builtin_fma(-g.wb, r, 1.0 + g.wb) * r;
+    }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double u = p[a] * s * g.s_d[a] + g.o_d[a];
+        const double u = __builtin_fma(p[a] * s, g.s_d[a], g.o_d[a]);
         const double fl = floor(u);
         if (!(fl >= 0.0)) { i[a] = 0; f[a] = 0.f; }              // below the box (or NaN)
         else if (fl > (double)(g.n[a] - 2)) { i[a] = g.n[a] - 2; f[a] = 1.f; }
