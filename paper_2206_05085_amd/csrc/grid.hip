@@ -513,6 +513,7 @@ __device__ __forceinline__ int64_t xcd_block(int nblocks) {
     return (int64_t)(blockIdx.x % N_XCD) * q + blockIdx.x / N_XCD;
 }
 
+// VEC: the vector path's sparse update (its dense one is tv_walk_kernel); otherwise the scalar path, dense or sparse
 template <bool VEC>
 __global__ __launch_bounds__(TV_BLOCK) void tv_kernel(DevGrid g, float coef, float delta, int dense, int64_t nvert,
                                                      int nblocks) {
@@ -532,13 +533,10 @@ __global__ __launch_bounds__(TV_BLOCK) void tv_kernel(DevGrid g, float coef, flo
     if (VEC) {
         float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
         if (live) q = *reinterpret_cast<const float4 *>(g.grad + base);
-        if (!dense) {
-            const bool nonzero = live && ((q.x != 0.f) | (q.y != 0.f) | (q.z != 0.f) | (q.w != 0.f));
-            const unsigned long long b = __ballot(nonzero);  // every lane takes part
-            const unsigned long long mine = ((1ull << G) - 1) << (vl * G);
-            if (!(b & mine)) return;
-        }
-        if (!live) return;
+        const bool nonzero = live && ((q.x != 0.f) | (q.y != 0.f) | (q.z != 0.f) | (q.w != 0.f));
+        const unsigned long long b = __ballot(nonzero);  // every lane takes part
+        const unsigned long long mine = ((1ull << G) - 1) << (vl * G);
+        if (!live || !(b & mine)) return;
         const float4 v = *reinterpret_cast<const float4 *>(g.data + base);
         const int64_t off[6] = {-(int64_t)g.sx, (int64_t)g.sx, -(int64_t)g.sy, (int64_t)g.sy, -(int64_t)g.cs,
                                 (int64_t)g.cs};
@@ -658,8 +656,8 @@ extern "C" int dvgo_tv_add_grad(const dvgo_grid *g, float weight, float delta, i
     const int nblocks = (int)((waves + TV_BLOCK / 64 - 1) / (TV_BLOCK / 64));
     const int launched = (nblocks + N_XCD - 1) / N_XCD * N_XCD;
     if (vec)
-        hipLaunchKernelGGL(tv_kernel<true>, dim3(launched), dim3(TV_BLOCK), 0, (hipStream_t)stream, dg, coef, delta,
-                           dense ? 1 : 0, nvert, nblocks);
+        hipLaunchKernelGGL(tv_kernel<true>, dim3(launched), dim3(TV_BLOCK), 0, (hipStream_t)stream, dg, coef, delta, 0,
+                           nvert, nblocks);
     else
         hipLaunchKernelGGL(tv_kernel<false>, dim3(launched), dim3(TV_BLOCK), 0, (hipStream_t)stream, dg, coef, delta,
                            dense ? 1 : 0, nvert, nblocks);

@@ -1501,9 +1501,9 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                 for (int g = 0; g < 8; ++g) dw3[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(d, h[g], dw3[g], 0, 0, 0);
             }
         };
-        // dz1 = mask(h1) W2^T dz2 of a tile (mask bits of parity pb, exponents g2/g1/ex of that
-        // tile), dfeat partials, dz1 in the dW1 frame
-        auto dz1_step = [&](const int g2[2], const int g1[2], const int ex[2], unsigned mbits, float (&dz1)[BWD_MP][2][4]) {
+        // dz1 = mask(h1) W2^T dz2 of a tile (its mask bits, exponents g2 and ex), kept in registers and written to
+        // the frame rows in the dW1 frame
+        auto dz1_step = [&](const int g2[2], const int ex[2], unsigned mbits, float (&dz1)[BWD_MP][2][4]) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;
             v4f acc[2][BWD_MP];  // [c][mp]
 #pragma unroll
@@ -1614,7 +1614,7 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
             if (it > 0) {
                 __builtin_amdgcn_s_setprio(3);  // 490 -> 473 us
                 float dz1[BWD_MP][2][4];
-                dz1_step(g2, g1, ex, mask_b[((it - 1) & 1) * (BWD_RW * 64) + w * 64 + ln], dz1);
+                dz1_step(g2, ex, mask_b[((it - 1) & 1) * (BWD_RW * 64) + w * 64 + ln], dz1);
                 // the raised priority is for the chain up to here, and the feature partials cover the way of
                 // the frame rows through LDS: 457 -> 440 us
                 __builtin_amdgcn_s_setprio(0);
