@@ -522,8 +522,7 @@ __device__ __forceinline__ void copy_to_lds(unsigned char *dst, const unsigned c
 // 143 -> 124, the rays' bias rows and the ray search by ray starts (instead of six dependent lane
 // shuffles) 124 -> 108.
 constexpr int FRS2 = 136;  // halves per W2 row in the forward's LDS (128 used)
-template <bool SPLIT>
-constexpr int FWD_WAVES = SPLIT ? 12 : 16;
+constexpr int FWD_WAVES = 12, FWD_THREADS = 64 * FWD_WAVES;
 
 // LDS row strides: a 16-byte read of 32 rows at one column runs without bank conflicts when the stride is
 // an odd multiple of 16 bytes.
@@ -551,7 +550,7 @@ __device__ __forceinline__ v16f mfma32(h8 a, h8 b, v16f c) {
 template <int GROUPS>
 __device__ __forceinline__ void copy_rows_to_lds(unsigned char *dst, int dstride, const unsigned char *src,
                                                  int sstride) {
-    for (int i = threadIdx.x; i < H * GROUPS; i += (int)blockDim.x) {
+    for (int i = threadIdx.x; i < H * GROUPS; i += FWD_THREADS) {
         const int r = i / GROUPS, u = i - r * GROUPS;
         const int from = 8 * (u >> 3) + 2 * (u & 3) + ((u >> 2) & 1), to = 4 * (u >> 2) + 2 * (u & 1) + ((u >> 1) & 1);
         *reinterpret_cast<uint2 *>(dst + r * dstride + 8 * to) =
@@ -591,9 +590,11 @@ __device__ __forceinline__ int ray_in_tile(const int *offs, int R, int r0, int w
 }
 
 // Channels c0 .. c0 + 3 and c1 .. c1 + 3 of a lookup, the bits of interp4 for each.  A corner's two loads
-// follow each other: they mostly touch the same line, which the L1 does not keep until a second pass where the
-// points are scattered (244,000 random points, both modes, eight loads of one part and then of the other: 51.8
-// and 45.1 us; this way 45.5 and 41.1).
+// follow each other: they mostly touch the same line, which the L1 does not keep until a second pass of eight
+// loads where neighbouring samples share no cells, as on rays of few samples: 300,000 samples, 6 a ray, split
+// 61 us in two passes, 57 this way, FP16 54 and 49.  Where they do share them the L1 keeps the lines, and the
+// upper half-wave's loads of the second part are for nothing: batches with bias rows (ray_rows) take two passes
+// (3,926,000 samples split 571 us, 575 this way, FP16 343 and 348; a training iteration on 981,504 1150 and 1158).
 __device__ __forceinline__ void interp4_pair(const DevGrid &g, const Tri &t, int c0, int c1, float4 &a, float4 &b) {
     const auto fma4 = [](float4 &acc, float w, const float4 &v) {
         acc.x = __builtin_fmaf(w, v.x, acc.x);
@@ -612,7 +613,7 @@ __device__ __forceinline__ void interp4_pair(const DevGrid &g, const Tri &t, int
 }
 
 template <bool SPLIT, int GM, bool ROWS>
-__global__ __launch_bounds__(64 * FWD_WAVES<SPLIT>) void mlp_fwd_kernel(MlpArgs a) {
+__global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
     static_assert(SPLIT || !ROWS, "the FP16 mode rounds the encoding");
     using L = FwdLds<SPLIT, ROWS>;
     constexpr int K1 = L::K1, FRS1 = L::RS1;
@@ -639,7 +640,7 @@ __global__ __launch_bounds__(64 * FWD_WAVES<SPLIT>) void mlp_fwd_kernel(MlpArgs 
     const int nwt = a.n_tiles;
     // neighbouring tiles go to neighbouring blocks: a small batch spreads over the CUs
     const int wt0 = blockIdx.x + (int)gridDim.x * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wstep = gridDim.x * FWD_WAVES<SPLIT>;
+    const int wstep = gridDim.x * FWD_WAVES;
     if (wt0 >= nwt) return;
     // First ray of a tile (past the last tile, the last tile's ray), read through the scalar cache: the
     // index is wave-uniform and the table is read-only here.
@@ -694,11 +695,12 @@ __global__ __launch_bounds__(64 * FWD_WAVES<SPLIT>) void mlp_fwd_kernel(MlpArgs 
         store_out();  // the previous tile's output
         if (GM) {
             const Tri t = trilinear<GM == 2>(a.fg, pt[0], pt[1], pt[2]);
-            in[0] = in[1] = none;
-            if (a.in_feat > 8) {
+            if ((SPLIT ? !ROWS : !a.rb) && a.in_feat > 8) {
                 interp4_pair(a.fg, t, 4 * hf, 8, in[0], in[1]);
             } else {
                 in[0] = interp4(a.fg, t, f0 ? 4 * hf : 0);
+                in[1] = none;
+                if (hf == 0) in[1] = interp4(a.fg, t, f1 ? 8 : 0);
             }
             if (a.feat_out && sv) {
                 float *fo = a.feat_out + (int64_t)s * a.in_feat;
@@ -1777,11 +1779,11 @@ template <int GM>
 int launch_fwd(const MlpArgs &a, const dvgo_color_mlp *m, hipStream_t st) {
     const dim3 grid(a.n_tiles < MAX_BLOCKS ? a.n_tiles : MAX_BLOCKS);
     if (m->precision == DVGO_MLP_F16)
-        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM, false>), grid, dim3(64 * FWD_WAVES<false>), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<false, GM, false>), grid, dim3(FWD_THREADS), 0, st, a);
     else if (a.rb)
-        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, true>), grid, dim3(64 * FWD_WAVES<true>), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, true>), grid, dim3(FWD_THREADS), 0, st, a);
     else
-        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, false>), grid, dim3(64 * FWD_WAVES<true>), 0, st, a);
+        hipLaunchKernelGGL((mlp_fwd_kernel<true, GM, false>), grid, dim3(FWD_THREADS), 0, st, a);
     return check_hip(hipGetLastError(), "mlp_fwd_kernel launch");
 }
 
