@@ -513,7 +513,6 @@ __device__ __forceinline__ int64_t xcd_block(int nblocks) {
     return (int64_t)(blockIdx.x % N_XCD) * q + blockIdx.x / N_XCD;
 }
 
-// VEC: the vector path's sparse update (its dense one is tv_walk_kernel); otherwise the scalar path, dense or sparse
 template <bool VEC>
 __global__ __launch_bounds__(TV_BLOCK) void tv_kernel(DevGrid g, float coef, float delta, int dense, int64_t nvert,
                                                      int nblocks) {
@@ -533,10 +532,13 @@ __global__ __launch_bounds__(TV_BLOCK) void tv_kernel(DevGrid g, float coef, flo
     if (VEC) {
         float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
         if (live) q = *reinterpret_cast<const float4 *>(g.grad + base);
-        const bool nonzero = live && ((q.x != 0.f) | (q.y != 0.f) | (q.z != 0.f) | (q.w != 0.f));
-        const unsigned long long b = __ballot(nonzero);  // every lane takes part
-        const unsigned long long mine = ((1ull << G) - 1) << (vl * G);
-        if (!live || !(b & mine)) return;
+        if (!dense) {
+            const bool nonzero = live && ((q.x != 0.f) | (q.y != 0.f) | (q.z != 0.f) | (q.w != 0.f));
+            const unsigned long long b = __ballot(nonzero);  // every lane takes part
+            const unsigned long long mine = ((1ull << G) - 1) << (vl * G);
+            if (!(b & mine)) return;
+        }
+        if (!live) return;
         const float4 v = *reinterpret_cast<const float4 *>(g.data + base);
         const int64_t off[6] = {-(int64_t)g.sx, (int64_t)g.sx, -(int64_t)g.sy, (int64_t)g.sy, -(int64_t)g.cs,
                                 (int64_t)g.cs};
@@ -583,9 +585,12 @@ __global__ __launch_bounds__(TV_BLOCK) void tv_kernel(DevGrid g, float coef, flo
 // planes along x, with the rows of x-1, x and x+1 in registers.  The plain kernel's x neighbours lie a plane
 // (1.2 MB at 160^2 x 12 channels) before and behind, and the gradient streaming through pushes them out of the
 // XCD's 4 MB L2; here the y and z neighbours are rows that the same XCD loaded one step ago.  Bound by memory:
-// 160^3 x 12 channels (590 MB) 158 -> 132 us, 100^3 30 -> 24.  Longer walks gain nothing (130 at 8 and 16
-// planes) and leave small grids with few waves (40^3: 9 us at 4 planes, 12 at 16).
+// 160^3 x 12 channels (590 MB) 143 -> 127 us, 100^3 30.1 -> 23.8, 64^3 8.4 -> 6.3.  Longer walks gain nothing.
+// A grid that the L2 holds has nothing to gain and loses waves (plain and walk: 16^3 x 12 3.2 and 3.8 us, 40^3
+// 4.0 and 4.3, 44^3 4.6 and 4.5, 48^3 5.3 and 5.0; 40^3 x 4 3.3 and 3.9, 64^3 x 4 both 4.4), and so has one
+// whose planes do not fill a block (20,000 x 3 x 3 x 12 6.8 and 9.1).
 constexpr int TV_RUN = 4;
+constexpr int64_t TV_WALK_FLOATS = 1 << 20;
 
 __global__ __launch_bounds__(TV_BLOCK) void tv_walk_kernel(DevGrid g, float coef, float delta, int colblocks, int nblocks) {
     const int64_t lb = xcd_block(nblocks);
@@ -643,9 +648,10 @@ extern "C" int dvgo_tv_add_grad(const dvgo_grid *g, float weight, float delta, i
     if (vec && (((uintptr_t)g->data | (uintptr_t)g->grad) & 15))
         return set_error(DVGO_ERR_SHAPE, "grid data and grad must be 16-byte aligned when ch_stride is a multiple of 4");
     const float coef = (float)(2.0 * (double)weight / ((double)nvert * g->channels));
+    const int64_t cols = (int64_t)g->ny * g->nz * (g->channels / 4);
     // (the sparse update reads no more than the gradient where nothing is to be done, vertex by vertex)
-    if (vec && dense) {
-        const int64_t cols = (int64_t)g->ny * g->nz * (g->channels / 4), cb = (cols + TV_BLOCK - 1) / TV_BLOCK;
+    if (vec && dense && nvert * g->channels >= TV_WALK_FLOATS && cols >= TV_BLOCK) {
+        const int64_t cb = (cols + TV_BLOCK - 1) / TV_BLOCK;
         const int64_t blocks = cb * ((g->nx + TV_RUN - 1) / TV_RUN);
         hipLaunchKernelGGL(tv_walk_kernel, dim3((unsigned)((blocks + N_XCD - 1) / N_XCD * N_XCD)), dim3(TV_BLOCK), 0,
                            (hipStream_t)stream, dg, coef, delta, (int)cb, (int)blocks);
@@ -656,8 +662,8 @@ extern "C" int dvgo_tv_add_grad(const dvgo_grid *g, float weight, float delta, i
     const int nblocks = (int)((waves + TV_BLOCK / 64 - 1) / (TV_BLOCK / 64));
     const int launched = (nblocks + N_XCD - 1) / N_XCD * N_XCD;
     if (vec)
-        hipLaunchKernelGGL(tv_kernel<true>, dim3(launched), dim3(TV_BLOCK), 0, (hipStream_t)stream, dg, coef, delta, 0,
-                           nvert, nblocks);
+        hipLaunchKernelGGL(tv_kernel<true>, dim3(launched), dim3(TV_BLOCK), 0, (hipStream_t)stream, dg, coef, delta,
+                           dense ? 1 : 0, nvert, nblocks);
     else
         hipLaunchKernelGGL(tv_kernel<false>, dim3(launched), dim3(TV_BLOCK), 0, (hipStream_t)stream, dg, coef, delta,
                            dense ? 1 : 0, nvert, nblocks);
