@@ -50,6 +50,17 @@ def _eager(*tensors) -> bool:
             and not torch.compiler.is_compiling())
 
 
+def _node(entry, *args):
+    """The node's outputs, or None where the call is not one for it (the Function serves it or says why): the
+    library refuses it, or the binding does not convert an argument's form (a box as a tensor, an iterator)."""
+    try:
+        return entry(*args)
+    except TypeError as e:
+        if "incompatible function arguments" not in str(e):
+            raise
+        return None
+
+
 def _vec(v):
     """Three numbers in any form the Functions take (sequence, array, tensor, iterator) as a tuple of floats."""
     return tuple(float(x) for x in v)
@@ -96,14 +107,12 @@ class RenderFn(torch.autograd.Function):
 
 
 def render(density, colour, batch, box, *, grid_color, act_shift, halt_T=0.0, bg=(1.0, 1.0, 1.0), want_dist=True):
-    box, bg = (_vec(box[0]), _vec(box[1])), _vec(bg)
-    if _eager(density, colour) and len(box[0]) == len(box[1]) == len(bg) == 3 and (native := _native()):
-        # None where the call is not one for the kernels: the Function then says why
-        out = native.render(density, colour, batch.ray_offsets, batch.xyz, batch.delta, batch.s_mid, batch.s_len,
-                               batch.n_rays, batch.n_samples, *box, bool(grid_color), act_shift, halt_T, bg, bool(want_dist))
+    if _eager(density, colour) and (native := _native()):
+        out = _node(native.render, density, colour, batch.ray_offsets, batch.xyz, batch.delta, batch.s_mid, batch.s_len,
+                    batch.n_rays, batch.n_samples, box[0], box[1], grid_color, act_shift, halt_T, bg, want_dist)
         if out is not None:
             return tuple(out)
-    return RenderFn.apply(density, colour, batch, box, grid_color, act_shift, halt_T, bg, want_dist)
+    return RenderFn.apply(density, colour, batch, (_vec(box[0]), _vec(box[1])), grid_color, act_shift, halt_T, _vec(bg), want_dist)
 
 
 class DistortionFn(torch.autograd.Function):
@@ -124,7 +133,7 @@ class DistortionFn(torch.autograd.Function):
 
 def distortion(w, ray_offsets, s_mid, s_len):
     if _eager(w, ray_offsets, s_mid, s_len) and (native := _native()):
-        loss = native.distortion(w, ray_offsets, s_mid, s_len)
+        loss = _node(native.distortion, w, ray_offsets, s_mid, s_len)
         if loss is not None:
             return loss
     return DistortionFn.apply(w, ray_offsets, s_mid, s_len)
@@ -151,12 +160,11 @@ class GatherFn(torch.autograd.Function):
 
 
 def gather(grid, xyz, box):
-    box = _vec(box[0]), _vec(box[1])
-    if _eager(grid, xyz) and len(box[0]) == len(box[1]) == 3 and (native := _native()):
-        out = native.gather(grid, xyz, *box)
+    if _eager(grid, xyz) and (native := _native()):
+        out = _node(native.gather, grid, xyz, box[0], box[1])
         if out is not None:
             return out
-    return GatherFn.apply(grid, xyz, box)
+    return GatherFn.apply(grid, xyz, (_vec(box[0]), _vec(box[1])))
 
 
 class ColorMLPFn(torch.autograd.Function):
@@ -182,7 +190,7 @@ class ColorMLPFn(torch.autograd.Function):
 
 def color_mlp(feat, W, b, ray_offsets, dirs, n_freq=4):
     if _eager(feat, *W, *b, ray_offsets, dirs) and (native := _native()):
-        rgb = native.color_mlp(feat, W[:3], b[:3], ray_offsets, dirs, n_freq)
+        rgb = _node(native.color_mlp, feat, W[:3], b[:3], ray_offsets, dirs, n_freq)
         if rgb is not None:
             return rgb
     return ColorMLPFn.apply(feat, W[0], b[0], W[1], b[1], W[2], b[2], ray_offsets, dirs, n_freq)
