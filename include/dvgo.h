@@ -325,8 +325,11 @@ int dvgo_grid_scatter(const dvgo_grid *g, int64_t n_samples, const float *xyz, c
 /* Brick-binned scatter (the same sum as dvgo_grid_scatter, organised for few, coalesced global
  * atomics).  dvgo_bin_samples sorts the samples by the 8^3-cell brick of the grid that holds
  * their cell (a counting sort into the caller's workspace of dvgo_bin_workspace_size bytes,
- * 256-byte aligned); dvgo_grid_scatter_binned then adds grad->g += trilinear^T(grad_out) brick
- * by brick, accumulating each brick in on-chip memory first.  The workspace must hold the bins
+ * 256-byte aligned; 12 bytes per sample and 8 per brick); dvgo_grid_scatter_binned then adds
+ * grad->g += trilinear^T(grad_out) brick by brick, accumulating each brick in on-chip memory first.
+ * That serves grids of one channel, and of two to four with at least 128 bricks; other grids are
+ * accepted, and their samples added in their own order, as dvgo_grid_scatter adds them, which merges
+ * vertices shared by consecutive samples only.  The workspace must hold the bins
  * of the same grid geometry (shape, box, warp) and the same xyz; grids with equal geometry can
  * share one binning.  Bins depend only on the points, so one binning serves every scatter of a
  * step. */
@@ -380,12 +383,15 @@ int dvgo_grid_resample(const dvgo_grid *src, int32_t nx, int32_t ny, int32_t nz,
 int dvgo_alpha(const dvgo_grid *density, int64_t n_samples, const float *xyz, const float *delta, float act_shift,
                float *alpha, void *stream);
 
-/* Workspace for the colour MLP (split weight image, per-ray direction encodings, tile
- * start rays and per-block weight-gradient partials). */
+/* Workspace for the colour MLP: split weight image (187 KB), per ray its direction encoding (144
+ * bytes) and, for batches of up to 8192 rays or at least 24 samples a ray, its layer-1 bias row
+ * (528 bytes), tile start rays, and per-block weight-gradient partials (at most 256 x 22 K floats).
+ * Its layout depends on n_rays and n_samples, so every call on it passes the same two. */
 int dvgo_mlp_workspace_size(const dvgo_color_mlp *m, int32_t n_rays, int64_t n_samples, size_t *bytes);
 
 /* The preparation every colour-MLP call starts with, alone: writes into ws the weights as scaled
- * FP16 planes, the view encodings of the rays and the first ray of each 32-sample tile, so that
+ * FP16 planes, the view encodings (and, where the workspace has them, bias rows) of the rays and the
+ * first ray of each 32-sample tile, so that
  * following calls on ws with the same weights and batch can set m->prepared (e.g. on another
  * stream, ahead of the feature gather).  Same arguments and workspace as dvgo_mlp_forward, minus
  * the features; m->prepared is ignored. */

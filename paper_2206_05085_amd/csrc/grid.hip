@@ -228,6 +228,11 @@ void launch_scatter(const DevGrid &dg, int64_t S, const float *xyz, const float 
         hipLaunchKernelGGL((scatter_kernel<NC, SL, false>), dim3(blocks), dim3(kBlock), 0, st, dg, S, xyz, gout, L);
 }
 
+// Slots a lane: a group has 8 / slots lanes per channel.  983,040 samples along rays, 1, 2, 4 and 8 slots, us: one
+// channel 110, 114, 122, 224; three 127, 125, 128, 189; four 119, 117, 119, 166; eight 136, 133, 134, 162; twelve
+// (at least two slots fit a wave) - , - , 199, 237; sixteen -, 167, 167, 167.  So one slot for one channel, where a
+// lane's atomics are the group's, and up to four elsewhere, where the choice is within 3%; fewer slots mean more
+// groups' ends in a wave and shorter rounds of staging.
 int scatter_any(const DevGrid &dg, int64_t S, const float *xyz, const float *gout, hipStream_t st) {
     if (dg.C == 1) launch_scatter<1, 1>(dg, S, xyz, gout, st);
     else if (dg.C <= 3) launch_scatter<3, 2>(dg, S, xyz, gout, st);
@@ -674,10 +679,10 @@ extern "C" int dvgo_tv_add_grad(const dvgo_grid *g, float weight, float delta, i
 //
 // The scatter of per-sample values into a grid, re-organised so that the global atomics are
 // few and coalesced.  Samples are binned by the 8^3-cell brick that holds their cell (a
-// counting sort: counts, an exclusive prefix, placement); then one block per brick adds its
-// samples' trilinear contributions into a 9^3-vertex LDS tile with LDS atomics and flushes the
-// tile with one global atomic per touched vertex channel, consecutive lanes on consecutive
-// addresses.  Consecutive samples lie along one ray and share a brick, so the counting passes
+// counting sort: counts, an exclusive prefix, placement); then, with up to four channels, one block
+// per brick adds its samples' trilinear contributions into a 9^3-vertex LDS tile with LDS atomics and
+// flushes the tile with one global atomic per touched vertex channel, consecutive lanes on consecutive
+// addresses (more channels: dvgo_grid_scatter_binned).  Consecutive samples lie along one ray and share a brick, so the counting passes
 // aggregate each run of equal bricks in the wave into one atomic.
 
 namespace {

@@ -517,10 +517,10 @@ __device__ __forceinline__ void copy_to_lds(unsigned char *dst, const unsigned c
 // Bound by the matrix and vector units together, which overlap by about half on this chip (measured: eight
 // 32 x 32 x 16 products and 56 FMAs of two waves take 188 ns where the products alone take 145 and the FMAs
 // 82), and by the clock, which falls to 1.8-1.9 GHz under them; with the lookup inside also by its loads.
-// 959,000 samples without the lookup 143 -> 105 us, 3,926,000 with it 626 -> 500-540 us.  Of that the larger
-// tiles (half the weight reads and matrix instructions of 16 x 16 x 32 tiles, K = 48 instead of 64) gave
-// 143 -> 124, the rays' bias rows and the ray search by ray starts (instead of six dependent lane
-// shuffles) 124 -> 108.
+// 981,900 samples without the lookup 136 -> 104 us against 16 x 16 x 32 tiles of 16 samples: the larger tiles (half
+// the weight reads and matrix instructions, K = 48 instead of 64) and the ray search by ray starts (instead of six
+// dependent lane shuffles) gave 136 -> 117, the rays' bias rows 117 -> 104.  3,926,000 along rays with the lookup
+// 550 -> 458.
 constexpr int FRS2 = 136;  // halves per W2 row in the forward's LDS (128 used)
 constexpr int FWD_WAVES = 12, FWD_THREADS = 64 * FWD_WAVES;
 
@@ -856,9 +856,13 @@ __global__ __launch_bounds__(FWD_THREADS) void mlp_fwd_kernel(MlpArgs a) {
 // the phases therefore hold independent work of up to three tiles.  dW1 reads only frame rows that its own
 // wave wrote, so it needs no barrier of its own; the sums over three outputs (logits, dz2, dW3) go to FP32
 // matrix instructions, since the vector ALU is the busier pipe (some 800 instructions a tile and SIMD, 1,400
-// before); and the C waves run dz1, the longest chain of phase 2, at a raised wave priority.  Feature, weight and
-// bias gradients of 981,504 samples: 554 us with four phases a tile, each a layer or a gradient, and the outputs'
-// sums on the vector ALU; 440 this way.
+// before); and the C waves run dz1, the longest chain of phase 2, at a raised wave priority.  981,504 samples, the
+// launch repeated back to back: 543 us with four phases a tile, each a layer or a gradient, and the outputs' sums
+// on the vector ALU; 437 this way (FP16 418 and 309).  Between other kernels, which leave other clocks and caches,
+// the same launch takes longer: 596 and 500 in an autograd pass, 480 to 500 in a training step.
+// The recompute of layer 1 multiplies the view encoding too (K = 64, split products), also where the forward took
+// the ray's bias row: the two agree to FP32 rounding, not bit for bit, so a unit within rounding of its kink may
+// be on here and off there.
 // Both roles run the same number of barriers, so s_barrier stays matched.
 
 constexpr int BWD_MP = 2;                   // 16-unit row tiles of one layer per wave
@@ -1159,8 +1163,8 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
         int F2 = FRAME_NONE;
         // inputs of a tile: global loads, in three steps spread over phases so that their
         // latency overlaps other work (ray window; ray search and feature loads; staging)
-        // The loaded values stay raw until stage_tile (phase D), where lanes past the last sample
-        // and the padding columns are zeroed, so that nothing consumes the loads before then.
+        // The loaded values stay raw until stage_tile (phase 1 of the next iteration), where lanes past the last
+        // sample and the padding columns are zeroed, so that nothing consumes the loads before then.
         float4 xlo = make_float4(0.f, 0.f, 0.f, 0.f), xhi = xlo;
         float grv = 0.f;
         unsigned xok = 0;  // bit 0: xlo is real, bit 1: xhi is real, bit 2: grv is real
@@ -1197,7 +1201,7 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
                 xok = 7u;
             }
         };
-        // ... and their split into the x plane of buffer pb (layer-1 B operand, read transposed by
+        // ... and their split into the x plane of buffer xs (layer-1 B operand, read transposed by
         // dW1), the sample's exponents and grad_rgb
         auto stage_tile = [&](int xs) {
             const int ln = fresh(lane()), xg = ln & 7, xsl = 8 * w + (ln >> 3);
@@ -1380,7 +1384,8 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
 #pragma unroll
                         for (int mp = 0; mp < BWD_MP; ++mp) acc[c][mp] = mfma16(w2h[mp][kk], bh[c], acc[c][mp]);
                 }
-                // W3 of output ln % 4 and this lane's units (a fourth row, never used, repeats the first)
+                // W3 of output ln % 4 and this lane's units (a fourth row repeats the first: its logit is formed and
+                // read as one, and its gradient is zero, as its upstream value is)
                 float4 wa[BWD_MP];
 #pragma unroll
                 for (int mp = 0; mp < BWD_MP; ++mp)
@@ -1466,7 +1471,7 @@ __global__ __launch_bounds__(BWD_THREADS) void mlp_bwd_kernel(MlpArgs a) {
 #pragma unroll
         for (int g = 0; g < 8; ++g) dw3[g] = v4f{0.f, 0.f, 0.f, 0.f};
         int F1 = FRAME_NONE, F2 = FRAME_NONE;
-        // dW1 += dz1^T x of a finished tile (its x buffer pb; both operands read transposed from the
+        // dW1 += dz1^T x of a finished tile (its x buffer xs; both operands read transposed from the
         // sample-major planes; logical inputs 0..47 in the three 16-column blocks)
         auto dw1_step = [&](int xs) {
             const int ln = fresh(lane()), j = ln & 15, q = ln >> 4;

@@ -226,9 +226,10 @@ __global__ __launch_bounds__(1024) void render_fwd_kernel(RenderArgs a) {
 }
 
 // DENS: the density gradient is scattered here; otherwise each sample's goes to grad_raw.  (Two kernels:
-// with both in one, the render_train of an unbounded batch of 2,293,760 samples took 200 us instead of 143.)
+// with both in one, the render_train of an unbounded batch of 2,293,760 samples took 200 us instead of 148; the
+// kernel with the lane-shift scatter took 140.)
 // The scatters are slot walks over each 64-sample chunk (walk_chunk): render_bwd of 1024 rays x 128 samples
-// on 32^3 grids 215 -> 21 us, of 981,504 samples on a 160^3 density grid 283 -> 118 us, where the chunk's
+// on 32^3 grids 214 -> 21 us, of 981,504 samples on a 160^3 density grid 283 -> 116 us, where the chunk's
 // shared vertices used to be merged by up to 63 lane shifts.  What bounds it now are the atomics.
 template <int MODE, bool WARP, bool DENS>
 __device__ __forceinline__ void render_bwd_ray(const RenderArgs &a, int r, const RayGrad &in) {

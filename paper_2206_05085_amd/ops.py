@@ -444,7 +444,8 @@ def bin_samples(grid: DeviceGrid, xyz, ws=None):
 
 
 def grid_scatter_binned(grid: DeviceGrid, xyz, grad_out, ws):
-    """grid.grad += trilinear^T(grad_out), brick by brick, with the bins of bin_samples."""
+    """grid.grad += trilinear^T(grad_out), brick by brick, with the bins of bin_samples (one channel, or two to
+    four and at least 128 bricks; other grids take grid_scatter's walk along the samples)."""
     _chk(xyz, "xyz", last=3)
     S = xyz.numel() // 3
     _chk(grad_out, "grad_out", numel=S * grid.struct().channels)
