@@ -130,11 +130,8 @@ __device__ __forceinline__ void warped_coords(const DevGrid &g, float x, float y
     } else {
         n = sqrt(__builtin_fma(p[2], p[2], __builtin_fma(p[0], p[0], p[1] * p[1])));
     }
-    double s = 1.0;
-    if (n > 1.0) {
-        const double r = 1.0 / n;
-        s = __builtin_fma(-g.wb, r, 1.0 + g.wb) * r;
-    }
+    const double r = 1.0 / n;  // the one division of the contraction
+    const double s = n > 1.0 ? __builtin_fma(-g.wb, r, 1.0 + g.wb) * r : 1.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const double u = __builtin_fma(p[a] * s, g.s_d[a], g.o_d[a]);
