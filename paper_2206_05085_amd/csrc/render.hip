@@ -106,9 +106,15 @@ __device__ __forceinline__ void load_sample(const RenderArgs &a, int k, bool has
 // lookup), and the optical depth and alpha follow from it exactly as in the forward.  The
 // points are read only where a cell is still needed: the colour grid's lookup and scatter, or
 // the density scatter inside the kernel.
+// Everything is requested before anything is used: with the intervals' loads after the softplus they waited for
+// the colours first (render_bwd of 64 rays x 2000 samples, the groups' join included, 126 -> 121 us).
 template <int MODE, bool WARP, bool DENS>
 __device__ __forceinline__ void load_sample_bwd(const RenderArgs &a, int k, bool has_next, SampleIn &s) {
     s.raw = a.raw_saved[k];
+    s.delta = a.delta[k];
+    s.m = a.s_mid[k];
+    s.l = a.s_len[k];
+    const float mn = a.s_mid[has_next ? k + 1 : k];
     if (MODE == DVGO_COLOR_GRID || DENS) {
         const float px = a.xyz[3 * k], py = a.xyz[3 * k + 1], pz = a.xyz[3 * k + 2];
         if (DENS) s.cd = cell_of<WARP>(a.dens, px, py, pz);
@@ -127,12 +133,9 @@ __device__ __forceinline__ void load_sample_bwd(const RenderArgs &a, int k, bool
     } else if (MODE != DVGO_COLOR_GRID) {
         s.c0 = s.c1 = s.c2 = 0.f;
     }
-    s.delta = a.delta[k];
     s.x = softplusf(s.raw + a.act_shift) * s.delta;
     s.alpha = -expm1f(-s.x);
-    s.m = a.s_mid[k];
-    s.l = a.s_len[k];
-    s.mn = has_next ? a.s_mid[k + 1] : 0.f;
+    s.mn = has_next ? mn : 0.f;
 }
 
 // What the forward of one ray leaves in registers (the same in every lane, and the values it
